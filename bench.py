@@ -504,7 +504,7 @@ def summarize_trace(folder):
         print(f"| `{name}` | {len(v)} | {sum(v) / len(v):.2f} | {v[len(v) // 2]:.2f} | "
               f"{v[0]:.2f} | {v[-1]:.2f} | {100 * sum(v) / total:.1f}% |")
     seq.sort()
-    starts = [q for q, e in enumerate(seq) if e[2].startswith("fht_reg_kernel")]
+    starts = [q for q, e in enumerate(seq) if e[2].startswith(("fht_reg_kernel", "fht_split_kernel"))]
     for q0 in reversed(starts):
         q1 = next((q for q in range(q0, len(seq)) if seq[q][2].startswith("walk")), None)
         if q1 is None or any(", true" in e[2] for e in seq[q0:q1 + 1]):

@@ -311,8 +311,9 @@ int fhtp_plan_destroy(fhtp_plan plan);
  *             bound of at most 8 shifts and no through-point pin (else two);
  *   stripe:   column tiles per stripe of the multi-step kernels' workgroup
  *             order, 1..64 (0: 16);
- *   fht_grid: 0: the FHT's resident grid loops over the work items; 1: one
- *             workgroup per work item;
+ *   fht_grid: of short bands (at most 16 rows of 8-bit pixels, 32 of 16-bit
+ *             ones), 0: the FHT's resident grid loops over the work items; 1:
+ *             one workgroup per work item (as taller bands always run);
  *   small:    0: a detection whose bands are at most 32 rows high and whose
  *             image, tables, value planes and back-pointers fit in 64 KB (and
  *             that has no through-point pin) runs as one workgroup doing the
@@ -355,7 +356,7 @@ int fhtp_tune_get(fhtp_tune_rule* out, int cap, int* count);
  *   launches and the gaps between them, plus a little time of its own.
  * fhtp_timing_stop: turns timing off, waits for every recorded event, and
  *   returns one entry per kernel family in order of first launch: the family
- *   name ("fht_reg_kernel", "fht_combine_kernel", "dp_pair_fixed",
+ *   name ("fht_reg_kernel" (the FHT's one-pass kernels), "fht_combine_kernel", "dp_pair_fixed",
  *   "dp_step_fixed", "dp_step_generic", "argmax_table", "walk",
  *   "angle_windows", "prep_kernel", ...), its launch count and the summed
  *   elapsed time of its brackets in milliseconds.  Up to `cap` entries

@@ -13,15 +13,18 @@
 // c = W-1-x for left-leaning ones).  Work per band and direction is p*n*W
 // additions, the O((w + h/k) * (h/k) * log(h/k)) cost of Section 2.1.
 //
-// Layout on gfx950: one thread owns one c-space column and keeps the n running
-// sums of that column in VGPRs through all p stages; the operand that comes
-// from another column (c + ceil(s/2)) is exchanged through LDS once per
-// stage.  A workgroup of NT threads covers NC columns (its waves overlap by a
-// few columns) and produces the NC - (n-1) leftmost of them (the rest are its
-// halo).  Global loads and table
-// stores are coalesced along x.  Bands taller than 2^7 rows run the same kernel
-// on 128-row sub-blocks, then a second kernel adds the sub-blocks along the
-// coarse levels of the recursion.
+// Layout on gfx950:
+//   - short bands (at most 16 rows of 8-bit pixels, 32 of 16-bit ones),
+//     fht_reg_kernel: one thread owns one c-space column and keeps the n
+//     running sums of that column in VGPRs through all p stages; the operand
+//     that comes from another column (c + ceil(s/2)) is exchanged through LDS
+//     once per stage;
+//   - taller ones, up to 128 rows of 8-bit pixels and 512 of 16-bit ones,
+//     fht_split_kernel: the fine and the coarse levels of a group of shifts
+//     run on lanes, and a sum goes through LDS once, in between;
+//   - the rest: fht_split_kernel on 128-row sub-blocks, then
+//     fht_combine_kernel adds the sub-blocks along the coarse levels.
+// Global loads and table stores are coalesced along x.
 #include <algorithm>
 #include <atomic>
 #include <vector>
@@ -64,7 +67,7 @@ constexpr int kLaneStages = 2;
 template <int P>
 struct RegCfg {
     static constexpr int N = 1 << P;
-    static constexpr int NT = (P >= 7) ? 512 : 256;
+    static constexpr int NT = 256;
     static constexpr int HALF = (N >= 2) ? N / 2 : 1;
     // Distinct columns of a workgroup: consecutive waves overlap by K columns
     // (see from_next_lane), so 64 - K per wave plus the last wave's K.
@@ -79,9 +82,6 @@ struct RegCfg {
     static constexpr int LDS_WORDS = (N >= 2) ? (SPARE + 1) * RW : 1;
     static constexpr int NPK = (N + 1) / 2;            // packed 16-bit pixel pairs per column
     static constexpr int NDIR = (P == 0) ? 1 : 2;      // one-row bands have only d = 0
-    // Fetch the next item's pixels during the current item's stages.  At
-    // n = 128 the 128 running sums leave no registers for it.
-    static constexpr bool PREFETCH = P <= 6;
 };
 
 // The lower operands of shifts 2t and 2t+1 of one stage are the same lower-
@@ -139,39 +139,7 @@ __device__ __forceinline__ void fht_stage(int32_t (&v)[N], int32_t* lds, int col
     }
 }
 
-// The same stage with no scheduling constraints: the compiler may issue all
-// LDS reads of the stage together (more registers, more memory parallelism).
-// In place, t downwards as above: a second array for the outputs made the
-// compiler spill registers at n = 128 (their scratch traffic showed up as
-// extra HBM writes).
-template <int N, int J, int RW>
-__device__ __forceinline__ void fht_stage_free(int32_t (&v)[N], int32_t* lds, int col, int wcol) {
-    constexpr int half = 1 << (J - 1);
-    constexpr int blocks = N >> J;
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < blocks; ++b)
-#pragma unroll
-        for (int t = 0; t < half; ++t) lds[wcol * RW + b * half + t] = v[b * 2 * half + half + t];
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < blocks; ++b) {
-#pragma unroll
-        for (int t = half - 1; t >= 0; --t) {
-            const int32_t a = v[b * 2 * half + t];
-            const int32_t x = lds[(col + t) * RW + b * half + t];
-            v[b * 2 * half + 2 * t + 1] = a + from_next_lane(x);
-            v[b * 2 * half + 2 * t] = a + x;
-        }
-    }
-    // The stage's sums are final here.  Integer adds reassociate freely, and
-    // without this the compiler carried partial sums of several stages at once
-    // (at n = 128 with 16-bit pixels: 256 VGPRs and 6 spilled; pinned: 188).
-#pragma unroll
-    for (int q = 0; q < N; ++q) asm volatile("" : "+v"(v[q]));
-}
-
-template <int N, int J, int P, int RW, bool GROUPED>
+template <int N, int J, int P, int RW>
 __device__ __forceinline__ void fht_stages(int32_t (&v)[N], int32_t* lds, int col, int wcol) {
     if constexpr (J <= P && J <= kLaneStages) {
         // Shifts 2t and 2t+1 add the lower block's shift t at columns c + t and
@@ -193,15 +161,14 @@ __device__ __forceinline__ void fht_stages(int32_t (&v)[N], int32_t* lds, int co
 #pragma unroll
             for (int q = 0; q < 2 * half; ++q) v[b * 2 * half + q] = o[q];
         }
+        // The stage's sums are final here.  Integer adds reassociate freely, and
+        // without this the compiler carries partial sums of several stages.
 #pragma unroll
-        for (int q = 0; q < N; ++q) asm volatile("" : "+v"(v[q]));  // as after an LDS stage
-        fht_stages<N, J + 1, P, RW, GROUPED>(v, lds, col, wcol);
+        for (int q = 0; q < N; ++q) asm volatile("" : "+v"(v[q]));
+        fht_stages<N, J + 1, P, RW>(v, lds, col, wcol);
     } else if constexpr (J <= P) {
-        if constexpr (GROUPED)
-            fht_stage<N, J, RW>(v, lds, col, wcol);
-        else
-            fht_stage_free<N, J, RW>(v, lds, col, wcol);
-        fht_stages<N, J + 1, P, RW, GROUPED>(v, lds, col, wcol);
+        fht_stage<N, J, RW>(v, lds, col, wcol);
+        fht_stages<N, J + 1, P, RW>(v, lds, col, wcol);
     }
 }
 
@@ -302,29 +269,7 @@ __device__ __forceinline__ void fetch_column(const FhtJob& J, int local, int col
     }
 }
 
-// Same pixels straight into the running-sum registers (no prefetch).
-template <int N, int NDIR, typename PixT>
-__device__ __forceinline__ void fetch_column_direct(const FhtJob& J, int local, int col,
-                                                    int32_t (&v)[N]) {
-    const FhtItem it = fht_decode<NDIR>(J, local, col);
-    const PixT* img = static_cast<const PixT*>(J.img);
-    const unsigned int row_bytes = (unsigned int)J.w * sizeof(PixT);
-    const __amdgpu_buffer_rsrc_t r =
-        make_rsrc(img + (size_t)it.blk * N * (size_t)J.w, (unsigned int)N * row_bytes);
-    // Lanes past the image read beyond the buffer extent, which returns 0.
-    const unsigned int voff = it.inside ? (unsigned int)it.ximg * sizeof(PixT) : 0x80000000u;
-    unsigned int so = 0;
-#pragma unroll
-    for (int y = 0; y < N; ++y) {
-        v[y] = (int32_t)buffer_pixel<PixT>(r, voff, so);
-        so += row_bytes;
-        asm volatile("" : "+s"(so));
-    }
-}
-
-// Output modes of a run:
-//   to_table: tables[blk][n-1 +- s][x] of a band of n = 2^P rows (d = 0 only from dir 0);
-//   else:     scratch[(blk*2 + dir)*2^P + s][c] in c-space (pass 1 of tall bands).
+// tables[blk][n-1 +- s][x] of a band of n = 2^P rows (d = 0 only from dir 0).
 template <int P>
 __device__ __forceinline__ void fht_store(const FhtJob& J, int local, int col,
                                           const int32_t (&v)[1 << P]) {
@@ -334,7 +279,7 @@ __device__ __forceinline__ void fht_store(const FhtJob& J, int local, int col,
     const int W = J.W;
     if (col >= J.T || it.c >= W) return;
     const unsigned int row_bytes = (unsigned int)W * 4u;
-    if (J.to_table && it.blk < J.narrow) {
+    if (it.blk < J.narrow) {
         // 16-bit table of a band whose line sums stay below 2^16
         constexpr int D = 2 * N - 1;
         const unsigned int row16 = (unsigned int)W * 2u;
@@ -358,7 +303,7 @@ __device__ __forceinline__ void fht_store(const FhtJob& J, int local, int col,
                 asm volatile("" : "+s"(so));
             }
         }
-    } else if (J.to_table) {
+    } else {
         constexpr int D = 2 * N - 1;
         const unsigned int voff = (unsigned int)(it.dir == 0 ? it.c : (W - 1 - it.c)) * 4u;
         const __amdgpu_buffer_rsrc_t r = make_rsrc(
@@ -380,39 +325,13 @@ __device__ __forceinline__ void fht_store(const FhtJob& J, int local, int col,
                 asm volatile("" : "+s"(so));
             }
         }
-    } else if (J.sub16) {
-        const unsigned int row16 = (unsigned int)W * 2u;
-        const __amdgpu_buffer_rsrc_t r = make_rsrc(
-            reinterpret_cast<uint16_t*>(J.out) + (size_t)(it.blk * C::NDIR + it.dir) * N * (size_t)W,
-            (unsigned int)N * row16);
-        const unsigned int voff = (unsigned int)it.c * 2u;
-        unsigned int so = 0;
-#pragma unroll
-        for (int s = 0; s < N; ++s) {
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v[s], r, (int)voff, (int)so, 0);
-            so += row16;
-            asm volatile("" : "+s"(so));
-        }
-    } else {
-        const __amdgpu_buffer_rsrc_t r =
-            make_rsrc(J.out + (size_t)(it.blk * C::NDIR + it.dir) * N * (size_t)W,
-                      (unsigned int)N * row_bytes);
-        const unsigned int voff = (unsigned int)it.c * 4u;
-        unsigned int so = 0;
-#pragma unroll
-        for (int s = 0; s < N; ++s) {
-            __builtin_amdgcn_raw_buffer_store_b32(v[s], r, (int)voff, (int)so, 0);
-            so += row_bytes;
-            asm volatile("" : "+s"(so));
-        }
     }
 }
 
 // Work item = (run, row block, direction, column tile).  The grid holds as
 // many workgroups as the chip keeps resident and loops over the items, so a
-// workgroup's table stores drain while it loads and transforms its next item;
-// the prefetching variants also fetch the next item's pixels while the
-// current one runs its stages.  A tile produces T columns (T <= NC - (n-1));
+// workgroup's table stores drain while it loads and transforms its next item,
+// and it fetches the next item's pixels while the current one runs its stages.  A tile produces T columns (T <= NC - (n-1));
 // the rest of its NC columns are halo.
 template <int P, typename PixT, int CAP>
 __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk) {
@@ -440,7 +359,7 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
     const int grid = (int)gridDim.x;
     int vi = blockIdx.x;
     int item = xmap(vi);
-    if constexpr (C::PREFETCH) {
+    {
         const int j = fht_find_job(pk, item);
         fetch_column<N, C::NPK, C::NDIR, PixT>(pk.job[j], item - pk.job[j].item0, col, pre);
     }
@@ -449,17 +368,13 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
         const FhtJob& J = pk.job[j];
         const int local = item - J.item0;
         int32_t v[N];
-        if constexpr (C::PREFETCH) {
 #pragma unroll
-            for (int q = 0; q < C::NPK; ++q) {
-                v[2 * q] = (int32_t)(pre[q] & 0xffffu);
-                if (2 * q + 1 < N) v[2 * q + 1] = (int32_t)(pre[q] >> 16);
-            }
-        } else {
-            fetch_column_direct<N, C::NDIR, PixT>(J, local, col, v);
+        for (int q = 0; q < C::NPK; ++q) {
+            v[2 * q] = (int32_t)(pre[q] & 0xffffu);
+            if (2 * q + 1 < N) v[2 * q + 1] = (int32_t)(pre[q] >> 16);
         }
         vi += grid;
-        if constexpr (C::PREFETCH) {
+        {
             // Unconditional prefetch (the last round re-reads its own item).
             const int nx = vi < total ? xmap(vi) : item;
             const int jn = fht_find_job(pk, nx);
@@ -477,18 +392,409 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
             int32_t pk[H];
 #pragma unroll
             for (int y = 0; y < H; ++y) pk[y] = v[y] | (v[y + H] << 16);
-            fht_stages<H, 1, P - 1, C::RW, C::PREFETCH>(pk, lds, col, wcol);
+            fht_stages<H, 1, P - 1, C::RW>(pk, lds, col, wcol);
 #pragma unroll
             for (int t = 0; t < H; ++t) {
                 v[t] = pk[t] & 0xffff;
                 v[t + H] = (int32_t)((uint32_t)pk[t] >> 16);
             }
-            fht_stages<N, P, P, C::RW, C::PREFETCH>(v, lds, col, wcol);  // the last stage, unpacked
+            fht_stages<N, P, P, C::RW>(v, lds, col, wcol);  // the last stage, unpacked
         } else {
-            fht_stages<N, 1, P, C::RW, C::PREFETCH>(v, lds, col, wcol);
+            fht_stages<N, 1, P, C::RW>(v, lds, col, wcol);
         }
         if (wr) fht_store<P>(J, local, col, v);
         if (vi < total) item = xmap(vi);
+    }
+}
+
+// ---- bands of 2^5 .. 2^9 rows ---------------------------------------------------
+//
+// The shifts s of a band are taken in groups that share their top Q bits g.
+// Inside a group the recursion splits into three parts:
+//
+//   - the first Q levels see only s >> (p-Q) .. = g, one line per block: R =
+//     2^Q rows are summed along the dyadic line of shift g (base sums);
+//   - the fine levels make, from NF = 2^LF base sums, the NF lines whose next
+//     LF bits are f.  Writing the shift at fine level j as g 2^j + f_j, its
+//     operand offset is g 2^(j-1) + ceil(f_j / 2): the first part adds up, over
+//     the levels, to g per base sum, so with base sum q read g q columns to the
+//     right what remains is the recursion of an NF-row band (shifts f_j);
+//   - the coarse levels join the M = 8 blocks of NF base sums in the same way:
+//     with block m of fine shift f read (g NF + f) m columns to the right, what
+//     remains is the recursion of an 8-row band, whose 8 shifts e are the
+//     band's shifts s = (g NF + f) 8 + e.
+//
+// So a workgroup makes one group of shifts of a column tile: phase 1 loads the
+// pixels at their skewed columns (a lane a column) and leaves the fine sums in
+// LDS; phase 2 reads them once at theirs (a lane two columns) and stores the 8
+// finished rows of a (g, f).  The small recursions run on lanes (a shift by a
+// column is a DPP wave shift), so a sum goes through LDS once, against once per
+// level in fht_reg_kernel, with one barrier, and no lane holds more than a few
+// dozen registers: two workgroups of 16 waves share a CU, and one's loads and
+// sums run beside the other's stores.  Its cost is that every group of shifts
+// reads the pixels again (from L1 and L2), that a wave's 64 columns give 57 (the
+// residual shifts reach 7 columns) and that a tile of 228 needs the fine sums
+// of 285.
+//
+// What bounds it: at 4096 x 4096, n = 128, 16-bit pixels (171 MB in and out)
+// 50 us a launch, 3.4 TB/s (fht_reg_kernel, one workgroup of 8 waves a CU on 147
+// KB of LDS: 63.5 us).  Timing copies: without the stores 31 us, without the
+// loads 37, phase 2 and its stores alone 28, phase 2 alone 15; so the stores
+// drain beside about half of the rest.  Streaming stores run in 42 us, but the
+// tables then miss the memory-side cache when the DP reads them (a detection
+// 177 against 171 us).  Two columns a lane in phase 1 (pairs of pixels from
+// aligned addresses, put in place with the next lane's) took 65 us, eight waves
+// a workgroup 58.
+//
+// 8-bit pixels: a lane's register holds the right-leaning line's sum in its
+// low half and the left-leaning line's in its high half (both directions are
+// the same recursion in c-space, at the same c) while the sums cover at most
+// 128 rows (at most 128 * 255 < 2^16, no carry between the halves) and the last
+// level of the band is still to come; the last levels run on 32 bits apart.
+template <int P>
+struct SplitCfg {
+    static constexpr int N = 1 << P;
+    static constexpr int LF = P >= 6 ? 3 : P - 3;  // fine levels
+    static constexpr int NF = 1 << LF;             // fine shifts (and base sums) of a block
+    static constexpr int Q = P - 3 - LF;           // levels in a base sum
+    static constexpr int R = 1 << Q;               // rows in a base sum
+    static constexpr int G = 1 << Q;               // groups of shifts
+    static constexpr int M = 8;                    // blocks
+    static constexpr int NT = P <= 7 ? 1024 : 512;
+    static constexpr int ROWS = NF * R;            // rows of a block
+    template <typename PixT>                       // pixels a lane holds of them
+    static constexpr int PX = ROWS * (sizeof(PixT) == 1 ? 2 : 1);
+    static constexpr int WC = 57;                  // columns a wave of phase 1 makes
+    static constexpr int CG = 5;                   // waves of phase 1 across
+    // columns a workgroup produces, in two waves' halves: what CG WC leaves
+    // after the skew f m and the residual shifts
+    static constexpr int FIT = (CG * WC - (NF - 1) * (M - 1) - 7) / 4 * 4;
+    static constexpr int TC = FIT < 240 ? FIT : 240;  // at most 120 of a half wave's 128 are whole
+    static constexpr int HC = TC / 2;
+    static constexpr int PITCH = CG * WC + 8;      // (a half wave reads past its columns)
+    // levels of phase 2 that 8-bit pixels run unpacked: the last one, and
+    // those whose sums cover more than 128 rows
+    static constexpr int UNPACKED = P <= 8 ? 1 : P - 7;
+};
+
+// One level of the recursion on the COLS (1 or 2) adjacent columns of a lane,
+// in place, shifts in order: the lower half-block's shift t is read t and t + 1
+// columns to the right.
+template <int ROWS, int COLS, int J>
+__device__ __forceinline__ void lane_stage(int32_t (&v)[ROWS][COLS]) {
+    constexpr int half = 1 << (J - 1);
+    // the columns one to the right
+    auto next = [](int32_t(&y)[COLS]) {
+        const int32_t z = from_next_lane(y[0]);
+        if constexpr (COLS == 2) y[0] = y[1];
+        y[COLS - 1] = z;
+    };
+#pragma unroll
+    for (int b = 0; b < (ROWS >> J); ++b) {
+        int32_t o[2 * half][COLS];
+#pragma unroll
+        for (int t = 0; t < half; ++t) {
+            const int32_t(&a)[COLS] = v[b * 2 * half + t];
+            int32_t y[COLS];
+#pragma unroll
+            for (int h = 0; h < COLS; ++h) y[h] = v[b * 2 * half + half + t][h];
+#pragma unroll
+            for (int q = 0; q < t; ++q) next(y);
+#pragma unroll
+            for (int h = 0; h < COLS; ++h) o[2 * t][h] = a[h] + y[h];
+            next(y);
+#pragma unroll
+            for (int h = 0; h < COLS; ++h) o[2 * t + 1][h] = a[h] + y[h];
+        }
+#pragma unroll
+        for (int q = 0; q < 2 * half; ++q)
+#pragma unroll
+            for (int h = 0; h < COLS; ++h) v[b * 2 * half + q][h] = o[q][h];
+    }
+    // final here, as in fht_stage_free
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+        for (int h = 0; h < COLS; ++h) asm volatile("" : "+v"(v[q][h]));
+}
+
+template <int ROWS, int COLS, int FROM, int TO>
+__device__ __forceinline__ void lane_stages(int32_t (&v)[ROWS][COLS]) {
+    if constexpr (FROM <= TO) {
+        lane_stage<ROWS, COLS, FROM>(v);
+        lane_stages<ROWS, COLS, FROM + 1, TO>(v);
+    }
+}
+
+// One item of the split kernel: a group of shifts g of a column tile (first
+// column ct) of row block blk, in direction dir (8-bit pixels: both).
+struct SplitItem {
+    int job, blk, dir, g, ct;
+};
+
+// The pixels of one wave of phase 1: the rows of block m at c-space column cb +
+// lane, base sum q read g (NF m + q) columns to its right (cb uniform); p[i]
+// of row i, 8-bit pixels the right-leaning column's in p[i] and the
+// left-leaning one's in p[ROWS + i].
+template <int P, typename PixT>
+__device__ __forceinline__ void split_load(const FhtJob& J, const SplitItem& it, int m, int cb,
+                                           uint32_t (&p)[SplitCfg<P>::template PX<PixT>]) {
+    using C = SplitCfg<P>;
+    constexpr int ROWS = C::ROWS;
+    constexpr int sz = (int)sizeof(PixT);
+    constexpr bool BOTH = sz == 1;
+    const int lane = threadIdx.x & 63;
+    const int w = J.w, W = J.W, g = it.g, dir = it.dir;
+    const int step = w * sz;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(
+        static_cast<const char*>(J.img) + ((size_t)it.blk * C::N + (size_t)m * ROWS) * (size_t)step,
+        (unsigned int)(ROWS * step));
+    // skew of row i of the block (i = ROWS: of the next block's first row)
+    auto skew = [&](int i) { return g * (i / C::R) + dyadic_offset(C::Q, g, i % C::R); };
+    const int cm = cb + g * C::NF * m;
+    const int reach = 63 + g * C::NF;          // to the last column any row reads
+    const bool in_right = cm + reach < w;      // every column is a pixel of the image
+    const bool in_left = cm >= W - w && cm + reach < W;
+    if (BOTH ? in_right && in_left : dir ? in_left : in_right) {
+        // one lane offset, rows and skews in the scalar offset
+        const int vr = lane * sz, vl = (63 - lane) * sz;
+        int ar = cm * sz, al = (W - 1 - 63 - cm) * sz;
+        if constexpr (BOTH) {
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                p[i] = buffer_pixel<PixT>(rs, (unsigned)vr, (unsigned)ar);
+                p[ROWS + i] = buffer_pixel<PixT>(rs, (unsigned)vl, (unsigned)al);
+                const int d = (skew(i + 1) - skew(i)) * sz;
+                ar += step + d;
+                al += step - d;
+                asm volatile("" : "+s"(ar), "+s"(al));
+            }
+        } else {
+            const int vo = dir ? vl : vr, sg = dir ? -1 : 1;
+            int at = dir ? al : ar;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                p[i] = buffer_pixel<PixT>(rs, (unsigned)vo, (unsigned)at);
+                at += step + sg * (skew(i + 1) - skew(i)) * sz;
+                asm volatile("" : "+s"(at));
+            }
+        }
+    } else {
+        // Byte offset of the pixel of c-space column c < 2 W; past the view
+        // outside the image, where loads return 0.
+        auto at = [&](int c, bool left) -> unsigned int {
+            const int cc = c >= W ? c - W : c;
+            const int x = left ? W - 1 - cc : cc;
+            return (unsigned)x < (unsigned)w ? (unsigned int)(x * sz) : 0x80000000u;
+        };
+        unsigned int so = 0;
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            const int c = cm + lane + skew(i);
+            p[i] = buffer_pixel<PixT>(rs, at(c, !BOTH && dir), so);
+            if constexpr (BOTH) p[ROWS + i] = buffer_pixel<PixT>(rs, at(c, true), so);
+            so += (unsigned int)step;
+            asm volatile("" : "+s"(so));
+        }
+    }
+}
+
+// The fine sums v[f] of those pixels.
+template <int P, typename PixT>
+__device__ __forceinline__ void split_fine(const uint32_t (&p)[SplitCfg<P>::template PX<PixT>],
+                                           int32_t (&v)[SplitCfg<P>::NF][1]) {
+    using C = SplitCfg<P>;
+#pragma unroll
+    for (int i = 0; i < C::ROWS; ++i) {
+        uint32_t t = p[i];
+        if constexpr (sizeof(PixT) == 1) t |= p[C::ROWS + i] << 16;
+        v[i / C::R][0] = i % C::R == 0 ? (int32_t)t : v[i / C::R][0] + (int32_t)t;
+    }
+    lane_stages<C::NF, 1, 1, C::LF>(v);
+}
+
+// The finished rows s = s0 .. s0 + 7 of one direction at tile columns c, c + 1
+// (those below `lim`), to the table or the sub-block scratch.
+template <int P, bool E16, bool REV>
+__device__ __forceinline__ void split_rows(char* base, int W, int x, bool two, bool skip0,
+                                           const int32_t (&v)[8][2]) {
+    constexpr int esz = E16 ? 2 : 4;
+    const unsigned int row = (unsigned int)W * esz;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, 8u * row);
+    unsigned int so = REV ? 7u * row : 0u;
+    const int xa = (REV && two ? x - 1 : x) * esz;
+    // the parity of a row's pairs is the same on every lane (c is even)
+    const int odd = __builtin_amdgcn_readfirstlane(
+        (int)(((uint32_t)reinterpret_cast<uintptr_t>(base) + (uint32_t)xa) >> 1));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (e > 0 || !skip0) {
+            const uint32_t a = (uint32_t)v[e][REV ? 1 : 0], b = (uint32_t)v[e][REV ? 0 : 1];
+            if (two) {
+                if constexpr (E16) {
+                    // one aligned 32-bit store, or two of 16 bits
+                    if (((odd + (REV ? 7 - e : e) * W) & 1) == 0) {
+                        __builtin_amdgcn_raw_buffer_store_b32(a | (b << 16), rs, xa, (int)so, 0);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)a, rs, xa, (int)so, 0);
+                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, rs, xa + 2, (int)so, 0);
+                    }
+                } else {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    u32x2 t;
+                    t.x = a;
+                    t.y = b;
+                    __builtin_amdgcn_raw_buffer_store_b64(t, rs, xa, (int)so, 0);
+                }
+            } else {
+                const uint32_t o = (uint32_t)v[e][0];
+                if constexpr (E16)
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)o, rs, xa, (int)so, 0);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b32(o, rs, xa, (int)so, 0);
+            }
+        }
+        so = REV ? so - row : so + row;
+    }
+}
+
+template <int P, bool E16, bool REV>
+__device__ __forceinline__ void split_cols(char* base, int W, int ct, int c, int lim, bool skip0,
+                                           const int32_t (&v)[8][2]) {
+    const int x = REV ? W - 1 - (ct + c) : ct + c;
+    if (c + 1 < lim)
+        split_rows<P, E16, REV>(base, W, x, true, skip0, v);
+    else if (c < lim)  // the last column of an odd tile
+        split_rows<P, E16, REV>(base, W, x, false, skip0, v);
+}
+
+template <int P, typename PixT>
+__device__ __forceinline__ void split_store(const FhtJob& J, int blk, int dir, int s0, int ct, int c,
+                                            int lim, const int32_t (&v)[8][2]) {
+    using C = SplitCfg<P>;
+    constexpr int N = C::N, D = 2 * N - 1;
+    const int W = J.W;
+    // The 8 rows' first one in memory: rows N-1 + s or, leaning left, N-1 - s
+    // of the table; row s of the scratch.
+    if (J.to_table) {
+        const bool skip0 = dir && s0 == 0;  // displacement 0 comes from the right-leaning lines
+        const int row = dir ? N - 1 - s0 - 7 : N - 1 + s0;
+        if constexpr (sizeof(PixT) == 1) {
+            if (blk < J.narrow) {
+                char* base = reinterpret_cast<char*>(J.out16 + ((size_t)blk * D + row) * (size_t)W);
+                if (dir)
+                    split_cols<P, true, true>(base, W, ct, c, lim, skip0, v);
+                else
+                    split_cols<P, true, false>(base, W, ct, c, lim, false, v);
+                return;
+            }
+        }
+        char* base =
+            reinterpret_cast<char*>(J.out + ((size_t)(blk - J.narrow) * D + row) * (size_t)W);
+        if (dir)
+            split_cols<P, false, true>(base, W, ct, c, lim, skip0, v);
+        else
+            split_cols<P, false, false>(base, W, ct, c, lim, false, v);
+    } else if constexpr (P == kRegMaxP) {
+        const size_t at = (((size_t)blk * 2 + dir) * N + s0) * (size_t)W;
+        if constexpr (sizeof(PixT) == 1)
+            split_cols<P, true, false>(reinterpret_cast<char*>(J.out) + at * 2, W, ct, c, lim, false, v);
+        else
+            split_cols<P, false, false>(reinterpret_cast<char*>(J.out) + at * 4, W, ct, c, lim, false, v);
+    }
+}
+
+// Item of workgroup b of the launch.  Workgroup b runs on XCD b % 8; each XCD
+// is dealt runs of kRun items, so that those that share pixel columns meet in
+// one L2 while the chip as a whole writes along one band at a time.  (Each XCD
+// on a contiguous eighth of the items, eight bands far apart being written at
+// once: 54.9 against 49.9 us at 4096 x 4096, n = 128, 16-bit pixels, 829
+// against 776 at 16384 x 16384; runs of 4: 50.4 and 813, of 64: 50.0 and 764.)
+// Tiles go from both ends in turn, as a left-leaning tile t covers the image
+// columns of right-leaning tile tiles - 1 - t.
+constexpr int kRun = 16;
+
+template <int P, bool BOTH, int CAP>
+__device__ __forceinline__ SplitItem split_item(const FhtPack<CAP>& pk, int b) {
+    using C = SplitCfg<P>;
+    const int xcd = b % kXcds, slot = b / kXcds;
+    const int whole = pk.total / (kXcds * kRun) * (kXcds * kRun);
+    const int item = b < whole ? slot / kRun * (kXcds * kRun) + xcd * kRun + slot % kRun : b;
+    SplitItem it;
+    it.job = __builtin_amdgcn_readfirstlane(fht_find_job(pk, item));
+    const FhtJob& J = pk.job[it.job];
+    int local = item - J.item0;
+    const int per_blk = (BOTH ? 1 : 2) * C::G * J.tiles;
+    it.blk = local / per_blk;
+    local -= it.blk * per_blk;
+    it.g = local & (C::G - 1);
+    const int u = local >> C::Q;
+    it.dir = BOTH ? 0 : u & 1;
+    const int tile = (u & 1) ? J.tiles - 1 - (u >> 1) : u >> 1;
+    it.ct = tile * J.T;
+    return it;
+}
+
+template <int P, typename PixT, int CAP>
+__global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_split_kernel(FhtPack<CAP> pk) {
+    using C = SplitCfg<P>;
+    constexpr bool BOTH = sizeof(PixT) == 1;
+    constexpr int WAVES = C::NT / 64;
+    __shared__ int32_t fine[C::M * C::NF * C::PITCH];  // [m][f][column]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SplitItem it = split_item<P, BOTH>(pk, (int)blockIdx.x);
+    const FhtJob& J = pk.job[it.job];
+    // Phase 1: a wave per (block, CG-th of the columns).  (The pixels of all
+    // of a wave's tasks loaded before the first one's sums: 53.6 against 50.1 us
+    // at 4096 x 4096, n = 128, 16-bit pixels.  The loads are not what it waits for.)
+#pragma unroll 1
+    for (int task = wave; task < C::M * C::CG; task += WAVES) {
+        const int m = task % C::M, cg = task / C::M;
+        uint32_t px[C::template PX<PixT>];
+        split_load<P, PixT>(J, it, m, it.ct + cg * C::WC, px);
+        int32_t v[C::NF][1];
+        split_fine<P, PixT>(px, v);
+        if (lane < C::WC) {
+#pragma unroll
+            for (int f = 0; f < C::NF; ++f)
+                fine[(m * C::NF + f) * C::PITCH + cg * C::WC + lane] = v[f][0];
+        }
+    }
+    __syncthreads();
+    // Phase 2: a wave per (f, half of the tile).
+    const int lim = min(J.T, J.W - it.ct);
+#pragma unroll 1
+    for (int task = wave; task < C::NF * 2; task += WAVES) {
+        const int f = task % C::NF, og = task / C::NF;
+        const int c = og * C::HC + 2 * lane;
+        int32_t v[8][2];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int32_t* src = &fine[(m * C::NF + f) * C::PITCH + c + f * m];
+            v[m][0] = src[0];
+            v[m][1] = src[1];
+        }
+        const int s0 = (it.g * C::NF + f) * 8;
+        const bool st = 2 * lane < C::HC;
+        if constexpr (BOTH) {
+            lane_stages<8, 2, 1, 3 - C::UNPACKED>(v);
+            int32_t r[8][2];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                r[e][0] = v[e][0] & 0xffff;
+                r[e][1] = v[e][1] & 0xffff;
+                v[e][0] = (int32_t)((uint32_t)v[e][0] >> 16);
+                v[e][1] = (int32_t)((uint32_t)v[e][1] >> 16);
+            }
+            lane_stages<8, 2, 4 - C::UNPACKED, 3>(r);
+            if (st) split_store<P, PixT>(J, it.blk, 0, s0, it.ct, c, lim, r);
+            lane_stages<8, 2, 4 - C::UNPACKED, 3>(v);
+            if (st) split_store<P, PixT>(J, it.blk, 1, s0, it.ct, c, lim, v);
+        } else {
+            lane_stages<8, 2, 1, 3>(v);
+            if (st) split_store<P, PixT>(J, it.blk, it.dir, s0, it.ct, c, lim, v);
+        }
     }
 }
 
@@ -681,17 +987,79 @@ hipError_t launch_reg_pack(const RegRun* runs, int count, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int P, typename PixT, int CAP>
+hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) {
+    using C = SplitCfg<P>;
+    FhtPack<CAP> pk{};
+    long long total = 0;
+    for (int q = 0; q < count; ++q) {
+        const RegRun& r = runs[q];
+        // The fewest tiles of at most TC columns, of equal (even) width.
+        const int tiles = (r.W + C::TC - 1) / C::TC;
+        FhtJob& J = pk.job[q];
+        J.img = r.img;
+        J.out = r.out;
+        J.w = r.w;
+        J.W = r.W;
+        J.tiles = tiles;
+        J.T = ((r.W + tiles - 1) / tiles + 1) & ~1;
+        J.item0 = (int)total;
+        J.to_table = r.to_table;
+        J.out16 = r.out16;
+        J.narrow = r.narrow;
+        J.sub16 = r.sub16;
+        total += (long long)tiles * r.blocks * C::G * (sizeof(PixT) == 1 ? 1 : 2);
+        if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    }
+    pk.count = count;
+    pk.total = (int)total;
+    if (total == 0) return hipSuccess;
+    // One workgroup per item: its stores drain while others load (a resident
+    // grid looping over the items makes an item's loads wait for the stores of
+    // the one before: 57.5 against 53.9 us at 4096 x 4096, n = 128, 16 bits).
+    {
+        TimedLaunch tl("fht_reg_kernel", stream);  // one family: the band transform
+        hipLaunchKernelGGL((fht_split_kernel<P, PixT, CAP>), dim3((unsigned)total), dim3(C::NT), 0,
+                           stream, pk);
+    }
+    return hipGetLastError();
+}
+
+// Largest band height (as a power of two) made in one pass, and the smallest
+// one the split kernel takes.  Measured at 4096 x 4096 (us; split, then the
+// register kernel or the two passes):
+//   8-bit:  n = 32 32.5 / 35.4, 64 30.3 / 38.6, 128 42.1 / 43.7 (15.1 / 17.2 at
+//           1024 x 1024), but 256 91 / 83, 512 131 / 109: every group of shifts
+//           loads the pixels again, a byte a lane;
+//   16-bit: n = 32 54.1 / 43.4, but 64 45.1 / 56.7, 128 50.3 / 59.0, 256 81 /
+//           116, 512 129 / 140.
+constexpr int one_pass_max(int dtype) { return dtype == 0 ? kRegMaxP : 8; }
+constexpr int split_min(int dtype) { return dtype == 0 ? 5 : 6; }
+
+template <int P, typename PixT, int CAP>
+hipError_t launch_one(const RegRun* runs, int count, hipStream_t stream) {
+    constexpr int dtype = sizeof(PixT) == 1 ? 0 : 1;
+    if constexpr (P > one_pass_max(dtype))
+        return hipErrorInvalidValue;
+    else if constexpr (P >= split_min(dtype))
+        return launch_split_pack<P, PixT, CAP>(runs, count, stream);
+    else
+        return launch_reg_pack<P, PixT, CAP>(runs, count, stream);
+}
+
 template <typename PixT, int CAP>
 hipError_t launch_reg_p(int p, const RegRun* runs, int count, hipStream_t stream) {
     switch (p) {
-        case 0: return launch_reg_pack<0, PixT, CAP>(runs, count, stream);
-        case 1: return launch_reg_pack<1, PixT, CAP>(runs, count, stream);
-        case 2: return launch_reg_pack<2, PixT, CAP>(runs, count, stream);
-        case 3: return launch_reg_pack<3, PixT, CAP>(runs, count, stream);
-        case 4: return launch_reg_pack<4, PixT, CAP>(runs, count, stream);
-        case 5: return launch_reg_pack<5, PixT, CAP>(runs, count, stream);
-        case 6: return launch_reg_pack<6, PixT, CAP>(runs, count, stream);
-        case 7: return launch_reg_pack<7, PixT, CAP>(runs, count, stream);
+        case 0: return launch_one<0, PixT, CAP>(runs, count, stream);
+        case 1: return launch_one<1, PixT, CAP>(runs, count, stream);
+        case 2: return launch_one<2, PixT, CAP>(runs, count, stream);
+        case 3: return launch_one<3, PixT, CAP>(runs, count, stream);
+        case 4: return launch_one<4, PixT, CAP>(runs, count, stream);
+        case 5: return launch_one<5, PixT, CAP>(runs, count, stream);
+        case 6: return launch_one<6, PixT, CAP>(runs, count, stream);
+        case 7: return launch_one<7, PixT, CAP>(runs, count, stream);
+        case 8: return launch_one<8, PixT, CAP>(runs, count, stream);
+        case 9: return launch_one<9, PixT, CAP>(runs, count, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -728,7 +1096,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         r.narrow = 0;
         r.grid_mode = J.grid_mode;
         r.sub16 = 0;
-        if (g.p <= kRegMaxP) {
+        if (g.p <= one_pass_max(J.dtype)) {
             r.p = g.p;
             r.blocks = g.k;
             r.to_table = 1;
@@ -744,7 +1112,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         runs.push_back(r);
     }
     for (int dtype = 0; dtype < 2; ++dtype) {
-        for (int p = 0; p <= kRegMaxP; ++p) {
+        for (int p = 0; p <= one_pass_max(dtype); ++p) {
             for (int gm = 0; gm < 2; ++gm) {
             std::vector<RegRun> group;
             for (const RegRun& r : runs)
@@ -762,7 +1130,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
     std::vector<CombineJob> comb;
     for (int q = 0; q < count; ++q) {
         const Geometry& g = jobs[q].g;
-        if (g.p <= kRegMaxP) continue;
+        if (g.p <= one_pass_max(jobs[q].dtype)) continue;
         CombineJob c;
         c.sub = jobs[q].scratch;
         c.sub16 = jobs[q].dtype == 0;
@@ -803,10 +1171,8 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
                     hipLaunchKernelGGL((fht_combine_kernel<2, uint16_t>), grid, block, 0, stream, pk);
                 else
                     hipLaunchKernelGGL((fht_combine_kernel<3, uint16_t>), grid, block, 0, stream, pk);
-            } else {
-                if (sh == 1)
-                    hipLaunchKernelGGL((fht_combine_kernel<1, int32_t>), grid, block, 0, stream, pk);
-                else if (sh == 2)
+            } else {  // 16-bit pixels: only bands of 512 and 1024 rows come here
+                if (sh == 2)
                     hipLaunchKernelGGL((fht_combine_kernel<2, int32_t>), grid, block, 0, stream, pk);
                 else
                     hipLaunchKernelGGL((fht_combine_kernel<3, int32_t>), grid, block, 0, stream, pk);
