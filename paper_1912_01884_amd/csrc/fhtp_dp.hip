@@ -59,7 +59,7 @@ namespace {
 
 constexpr int kWaves = 4;      // waves per workgroup, one displacement chunk each
 constexpr int kMaxFixedB = 16; // largest bend bound with a register-window kernel
-constexpr int kDCGeneric = 8;  // displacements per thread in the scanning kernels
+constexpr int kDCGeneric = 8;  // displacements per thread in argmax_table
 constexpr int kPack = 256;     // images per launch (kernel arguments of up to 32 KB)
 constexpr int kXcds = 8;       // accelerator dies of the MI355X, each with its own L2
 
@@ -81,7 +81,7 @@ struct DpJob {
     const int32_t* win;       // mode-1 windows lo[D], hi[D], or null
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w;
-    int bound;    // mode-0 bound (scanning kernel)
+    int bound;    // mode-0 bound (block kernel)
     int full;     // windows cover every displacement
     int items_x;  // workgroups along x
     int items_y;  // workgroups along the displacements
@@ -335,45 +335,7 @@ using PairLinks = std::conditional_t<sizeof(AT) == 1, uint16_t, uint32_t>;
 template <typename AT>
 constexpr int kLinkBits = 8 * (int)sizeof(AT);
 
-// Byte offset of a row inside the view (0 for rows it does not cover, whose
-// lanes are masked by an out-of-range lane offset instead).
-__device__ __forceinline__ unsigned int row_off(const RowView& v, int row, int pitch, int esz) {
-    return (row >= v.base && row < v.end) ? (unsigned int)(row - v.base) * pitch * esz : 0u;
-}
-
 constexpr unsigned int kOut = 0x80000000u;  // lane offset past every view: loads 0, stores drop
-
-// One output cell (x' = xp, displacement d) with range maximum m reached at
-// row ra, stored through the views of the wave's rows of V_i (ov) and
-// A_{i+1} (av).
-template <typename AT>
-__device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const RowView& av, int m,
-                                     int ra, int hval, int xp, int d, Best& best) {
-    const int n = a.n, w = a.w;
-    const int D = 2 * n - 1;
-    const int r = d + n - 1;
-    if (xp >= w || r >= D) return;
-    const bool last = a.key != nullptr;
-    if (!last) {
-        const unsigned int arow = row_off(av, r, a.a_pitch, sizeof(AT));
-        const unsigned int aval = (unsigned int)(ra < 0 ? 0 : ra);
-        if constexpr (sizeof(AT) == 1)
-            __builtin_amdgcn_raw_buffer_store_b8((unsigned char)aval, av.rs, xp, (int)arow,
-                                                 kStoreScope);
-        else
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)aval, av.rs, xp * 2, (int)arow,
-                                                  kStoreScope);
-    }
-    const int x = xp - d;
-    if (x < 0 || x >= w) return;
-    const int val = (m >= 0 && (a.out_pin_x < 0 || x == a.out_pin_x)) ? hval + m : -1;
-    if (last) {
-        take_best(best, pack_key(val, x, r, D), ra);
-    } else {
-        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.v_pitch, 4),
-                                              kStoreScope);
-    }
-}
 
 // Sliding maximum of the windows [j, j + 2B] of v, j = 0 .. DC-1, with the
 // smallest index reaching it: each window is split at a block start b in
@@ -1163,197 +1125,59 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     }
 }
 
-// Step with per-displacement windows [lo(d), hi(d)] (large mode-0 bounds, the
-// angle form, no bound at all).  Both window ends are non-decreasing in d, so
-// the windows of a wave's kDCGeneric displacements fall into groups that
-// share a point c (c = hi of the group's first window): each window of a
-// group is [lo, c] + [c+1, hi].  One descending scan from c gives every
-// [lo, c] maximum (recorded as the scan passes each lo) and one ascending scan
-// from c+1 gives every [c+1, hi] maximum, so each V cell of the union of the
-// windows is read and compared once, with the loads issued eight at a time.
-// Ties keep the smallest d' (descending scans take equal values, ascending
-// ones only larger values, and the [lo, c] part wins ties).
-constexpr int kScanTile = 8;
+// Step with per-displacement windows [lo(d), hi(d)] (mode-0 bounds above the
+// fixed-window kernels', the angle form, and with a through-point pin no bound
+// at all): a workgroup owns COLS successor columns x' and every displacement
+// row (D < ROWS), so each cell of V_{i+1} is loaded once however many windows
+// hold it.  The rows are cut into blocks of kBlk.  A thread loads one block of
+// one column and leaves in LDS its cells and their maxima from the block's start
+// down to every row (prefix) and from every row to its end (suffix), each with
+// the smallest row reaching it; the maxima of runs of 1, 2, 4, .. whole blocks
+// follow.  A window [lo, hi] inside one block is scanned directly (at most kBlk
+// cells); one that crosses blocks is the suffix at lo, at most two overlapping
+// runs of the whole blocks between, and the prefix at hi, taken in that order
+// with a later candidate winning only when larger, so ties keep the smallest d'
+// as everywhere else.  O(1) work per cell after O(D) per column, for any windows.
+//
+// What bounds it: the chain of a launch.  At 4096 columns of 255 displacements
+// 7.8 us a launch, of which (timing copies) the loads take 2.0, the stores 1.5
+// (the planes written through to memory: 0.5 more) and the window maxima 1.0;
+// the rest is the launch itself and its barriers.  Scanning the loaded rows in
+// registers and taking an interior tile's addresses from one lane offset per
+// plane took it from 8.3.  511 displacements at w = 2047: 8.3 us (a scan of every
+// window by the wave, each cell loaded once per 8 displacements: 20.8).
+constexpr int kBlk = 16;             // rows per block
 constexpr int kEmpty = -2147483647 - 1;  // no cell yet (below every V, -1 included)
 
-template <typename AT, int CAP, typename TT>
-__global__ __launch_bounds__(64 * kWaves) void dp_step_generic(DpPack<CAP> pk) {
-    __shared__ int res_v[kWaves][kDCGeneric][64];
-    __shared__ int res_i[kWaves][kDCGeneric][64];
-    const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);  // as dp_step_fixed
-    const int jj = dp_find_job(pk, it);
-    const DpJob& a = pk.job[jj];
-    const int local = it - a.item0;
-    const int bx = local / a.items_y, by = local - bx * a.items_y;
-    const int n = a.n, w = a.w;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int xp = bx * 64 + lane;
-    const int chunk = by * kWaves + wave;
-    const int d0 = -(n - 1) + chunk * kDCGeneric;
-    const int D = 2 * n - 1;
-    const int jn = min(kDCGeneric, D - (d0 + n - 1));  // displacements of this wave
-    const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
-    const bool last = a.key != nullptr;  // no planes to write (views unused)
-    const RowView ov = row_view(last ? a.vin : a.vout, a.v_pitch, 4, d0 + n - 1, kDCGeneric, D);
-    const RowView av = row_view(last ? a.vin : a.aout, a.a_pitch, sizeof(AT), d0 + n - 1,
-                                kDCGeneric, D);
-    int hv[kDCGeneric];
-#pragma unroll
-    for (int j = 0; j < kDCGeneric; ++j) hv[j] = load_h<TT>(a, xp, d0 + j);
-    // The wave's windows, one per lane (lanes 0 .. kDCGeneric-1), read back as
-    // scalars with readlane: no memory access inside the scans.
-    int wlo = 0, whi = 0;
-    {
-        const int dl = d0 + min(lane, kDCGeneric - 1);
-        window_of(n, a.full, a.win, a.bound, min(dl, n - 1), wlo, whi);
+template <int ROWS, int COLS>
+struct BlkCfg {
+    static constexpr int NB = ROWS / kBlk;
+    static constexpr int CELLS = ROWS * COLS;
+    static constexpr int THREADS = CELLS < 1024 ? CELLS : 1024;
+    static constexpr int OUT = CELLS / THREADS;    // cells per thread
+    static constexpr int LANES = THREADS / COLS;   // row lanes
+    static constexpr int levels() {                // runs of 1, 2, .. < NB blocks
+        int l = 1;
+        while ((1 << l) < NB) ++l;
+        return l;
     }
-    auto lo_of = [&](int j) { return __builtin_amdgcn_readlane(wlo, j); };
-    auto hi_of = [&](int j) { return __builtin_amdgcn_readlane(whi, j); };
-    if (a.full) {
-        // Section 2.2: every window is the whole column, so the workgroup's
-        // waves split the column's rows, and the smallest row reaching the
-        // maximum wins across them (ties to the lower wave).
-        __shared__ int col_v[kWaves][64];
-        __shared__ int col_i[kWaves][64];
-        const int rows = (D + kWaves - 1) / kWaves;
-        const int r_lo = wave * rows, r_hi = min(D, r_lo + rows);
-        int cv = kEmpty, ci = 0;
-        for (int t0 = r_lo; t0 < r_hi; t0 += kScanTile) {
-            int v[kScanTile];
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q)
-                v[q] = load_v(a.vin, a.vin_pitch, xp, t0 + q - (n - 1), n, mk);
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q) {
-                const bool take = t0 + q < r_hi && v[q] > cv;
-                cv = take ? v[q] : cv;
-                ci = take ? t0 + q - (n - 1) : ci;
-            }
-        }
-        col_v[wave][lane] = cv;
-        col_i[wave][lane] = ci;
-        __syncthreads();
-        int m = col_v[0][lane], ia = col_i[0][lane];
-#pragma unroll
-        for (int q = 1; q < kWaves; ++q) {
-            const bool take = col_v[q][lane] > m;
-            m = take ? col_v[q][lane] : m;
-            ia = take ? col_i[q][lane] : ia;
-        }
-        Best best;
-#pragma unroll
-        for (int j = 0; j < kDCGeneric; ++j) {
-            if (j >= jn) break;
-            emit<AT>(a, ov, av, m, ia + n - 1, hv[j], xp, d0 + j, best);
-        }
-        finish(a, best, local);
-        return;
-    }
-    for (int ja = 0; ja < jn;) {
-        const int c = hi_of(ja);
-        int jb = ja;
-        while (jb + 1 < jn && lo_of(jb + 1) <= c) ++jb;
-        // [lo_j, c], descending; record at each lo_j (j = jb down to ja)
-        const int first = lo_of(ja);
-        int cv = kEmpty, ci = c;
-        int p = jb, plo = lo_of(jb);
-        for (int t0 = c; t0 >= first; t0 -= kScanTile) {
-            int v[kScanTile];
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q) v[q] = load_v(a.vin, a.vin_pitch, xp, t0 - q, n, mk);
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q) {
-                const int dp = t0 - q;
-                if (dp < first) break;
-                const bool take = v[q] >= cv;
-                cv = take ? v[q] : cv;
-                ci = take ? dp : ci;
-                while (p >= ja && plo == dp) {
-                    res_v[wave][p][lane] = cv;
-                    res_i[wave][p][lane] = ci;
-                    --p;
-                    plo = p >= ja ? lo_of(p) : kEmpty;
-                }
-            }
-        }
-        // [c+1, hi_j], ascending; record at each hi_j (j = ja up to jb)
-        const int last = hi_of(jb);
-        cv = kEmpty;
-        ci = c;
-        p = ja;
-        int phi = hi_of(ja);
-        auto record_up = [&](int at) {
-            while (p <= jb && phi == at) {
-                const int sv = res_v[wave][p][lane];
-                const bool up = cv > sv;  // the [lo, c] part wins ties
-                res_v[wave][p][lane] = up ? cv : sv;
-                if (up) res_i[wave][p][lane] = ci;
-                ++p;
-                phi = p <= jb ? hi_of(p) : kEmpty;
-            }
-        };
-        record_up(c);
-        for (int t0 = c + 1; t0 <= last; t0 += kScanTile) {
-            int v[kScanTile];
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q) v[q] = load_v(a.vin, a.vin_pitch, xp, t0 + q, n, mk);
-#pragma unroll
-            for (int q = 0; q < kScanTile; ++q) {
-                const int dp = t0 + q;
-                if (dp > last) break;
-                const bool take = v[q] > cv;
-                cv = take ? v[q] : cv;
-                ci = take ? dp : ci;
-                record_up(dp);
-            }
-        }
-        ja = jb + 1;
-    }
-    Best best;
-#pragma unroll
-    for (int j = 0; j < kDCGeneric; ++j) {
-        if (j >= jn) break;
-        const int m = res_v[wave][j][lane];
-        const int ia = res_i[wave][j][lane];
-        emit<AT>(a, ov, av, m, ia + n - 1, hv[j], xp, d0 + j, best);
-    }
-    finish(a, best, local);
-}
+};
 
-// Step with per-displacement windows for bands of at most 255 displacements
-// and no pin (the angle form, mode-0 bounds above 16): a workgroup owns
-// kBlkCols successor columns x' and every displacement row, so each cell of
-// V_{i+1} is loaded once, into LDS, however many windows hold it.  The rows
-// are cut into blocks of kBlk; per column the workgroup keeps the maxima
-// from each block's start down to every row (prefix) and from every row to
-// its block's end (suffix), each with the smallest row reaching it, and a
-// sparse table of the block maxima over 1, 2, 4 and 8 consecutive blocks.
-// A window [lo, hi] inside one block is scanned directly (at most kBlk
-// cells); one that crosses blocks is the suffix at lo, at most two
-// overlapping runs of whole blocks, and the prefix at hi, taken in that
-// order with a later candidate winning only when larger, so ties keep the
-// smallest d' as everywhere else.
-constexpr int kBlkCols = 16;      // successor columns per workgroup
-constexpr int kBlk = 16;          // rows per block
-constexpr int kBlkRows = 256;     // rows held: D <= 255
-constexpr int kBlkLevels = 4;     // block runs of 1, 2, 4 and 8
-constexpr int kBlkThreads = 1024; // 16 waves: four per SIMD hide the LDS round trips
-constexpr int kBlkLanes = kBlkThreads / kBlkCols;  // row lanes
-constexpr int kBlkOut = kBlkRows / kBlkLanes;      // rows (cells) per thread
-
-template <typename AT, int CAP, typename TT>
-__global__ __launch_bounds__(kBlkThreads) void dp_step_blocks(DpPack<CAP> pk) {
-    constexpr int NB = kBlkRows / kBlk;
-    static_assert(NB * kBlkCols <= kBlkThreads, "one block scan per thread");
-    __shared__ int vt[kBlkRows][kBlkCols];       // V_{i+1}(X0 + c, row r), -1 where none
-    __shared__ int pre_v[kBlkRows][kBlkCols];    // max over [block start, r]
-    __shared__ int suf_v[kBlkRows][kBlkCols];    // max over [r, block end]
-    __shared__ unsigned char pre_i[kBlkRows][kBlkCols];  // its smallest row
-    __shared__ unsigned char suf_i[kBlkRows][kBlkCols];
-    __shared__ int run_v[kBlkLevels][NB][kBlkCols];  // max over blocks [b, b + 2^l)
-    __shared__ unsigned char run_i[kBlkLevels][NB][kBlkCols];
-    __shared__ unsigned char wlo[kBlkRows], whi[kBlkRows];  // window of each row, as rows
+template <int ROWS, int COLS, typename AT, int CAP, typename TT>
+__global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(DpPack<CAP> pk) {
+    using C = BlkCfg<ROWS, COLS>;
+    constexpr int NB = C::NB, LV = C::levels();
+    // row r of column c at r * COLS + c, blocks COLS words apart (the lanes of a
+    // wave that scan different blocks of the same columns hit other banks)
+    constexpr int SIZE = C::CELLS + NB * COLS;
+    __shared__ int vt[SIZE];                   // V_{i+1}(X0 + c, row r), -1 where none
+    __shared__ int pre_v[SIZE];                // max over [block start, r]
+    __shared__ int suf_v[SIZE];                // max over [r, block end]
+    __shared__ unsigned char ps_i[C::CELLS];   // their smallest rows in the block: pre, suf << 4
+    __shared__ int run_v[LV][NB][COLS];        // max over blocks [b, b + 2^l)
+    __shared__ unsigned short run_i[LV][NB][COLS];
+    __shared__ unsigned short wlo[ROWS], whi[ROWS];  // window of each row, as rows
+    auto at = [](int r, int c) { return r * COLS + c + (r / kBlk) * COLS; };
 
     const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     const int jj = dp_find_job(pk, it);
@@ -1361,82 +1185,107 @@ __global__ __launch_bounds__(kBlkThreads) void dp_step_blocks(DpPack<CAP> pk) {
     const int local = it - a.item0;  // the column tile
     const int n = a.n, w = a.w, D = 2 * n - 1;
     const int t = threadIdx.x;
-    const int c = t & (kBlkCols - 1);
-    const int rq = t / kBlkCols;  // first row of the thread's rows rq, rq + kBlkLanes, ...
-    const int xp = local * kBlkCols + c;
+    const int c = t % COLS;
+    const int rq = t / COLS;  // first row of the thread's cells rq, rq + LANES, ...
+    const int xp = local * COLS + c;
 
-    if (t < D) {
-        int lo, hi;
-        window_of(n, a.full, a.win, a.bound, t - (n - 1), lo, hi);
-        wlo[t] = (unsigned char)(lo + n - 1);
-        whi[t] = (unsigned char)(hi + n - 1);
-    }
-    // H_i(x' - d, d) of the thread's cells, then its rows of V_{i+1}
-    int hv[kBlkOut];
+    // A tile whose every cell, window row and successor lies inside the image
+    // (and carries no pin) takes its addresses from one lane offset per plane.
+    const int X0 = local * COLS;
+    const bool inner = D == ROWS - 1 && a.vin_pin == 0 && X0 - (n - 1) >= 0 &&
+                       X0 + COLS - 1 + (n - 1) < w &&
+                       (unsigned long long)D * (unsigned)max(a.h_pitch, a.vin_pitch) < (1u << 30);
+    // H_i(x' - d, d) of the thread's cells, in flight during the scans
+    int hv[C::OUT];
+    if (inner) {
+        const TT* h = static_cast<const TT*>(a.htab);
+        const unsigned int o = (unsigned int)(rq * (a.h_pitch - 1) + xp + n - 1);
 #pragma unroll
-    for (int j = 0; j < kBlkOut; ++j) hv[j] = load_h<TT>(a, xp, rq + kBlkLanes * j - (n - 1));
-    const DRange mk = drange(n, xp, VMask{0, w, 0, w});
+        for (int j = 0; j < C::OUT; ++j) {
+            // (the table's rows end at D - 1: the tile's last row reads the one above)
+            const bool pad = j == C::OUT - 1 && rq + C::LANES * j >= D;
+            hv[j] = (int)(h + (ptrdiff_t)(C::LANES * j) * (a.h_pitch - 1))[pad ? o - a.h_pitch : o];
+        }
+    } else {
 #pragma unroll
-    for (int j = 0; j < kBlkOut; ++j) {
-        const int r = rq + kBlkLanes * j;
-        vt[r][c] = load_v(a.vin, a.vin_pitch, xp, r - (n - 1), n, mk);  // -1 past row D-1
+        for (int j = 0; j < C::OUT; ++j) hv[j] = load_h<TT>(a, xp, rq + C::LANES * j - (n - 1));
     }
-    __syncthreads();
     if (rq < NB) {
         // block rq of column c: prefix maxima ascending (ties keep the first),
         // suffix maxima descending (ties move to the smaller row)
         const int r0 = rq * kBlk;
-        int pv = kEmpty, pi = r0;
+        int v[kBlk];
+        if (inner) {
+            const unsigned int o = (unsigned int)(r0 * a.vin_pitch + xp);
+#pragma unroll
+            for (int q = 0; q < kBlk; ++q) {
+                const bool pad = q == kBlk - 1 && r0 + q >= D;
+                const int u = (a.vin + (ptrdiff_t)q * a.vin_pitch)[pad ? o - a.vin_pitch : o];
+                v[q] = pad ? -1 : u;
+            }
+        } else {
+            const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
+#pragma unroll
+            for (int q = 0; q < kBlk; ++q)
+                v[q] = load_v(a.vin, a.vin_pitch, xp, r0 + q - (n - 1), n, mk);  // -1 past row D-1
+        }
+        int sv[kBlk], si[kBlk];
+        sv[kBlk - 1] = v[kBlk - 1];
+        si[kBlk - 1] = kBlk - 1;
+#pragma unroll
+        for (int q = kBlk - 2; q >= 0; --q) {
+            const bool take = v[q] >= sv[q + 1];
+            sv[q] = take ? v[q] : sv[q + 1];
+            si[q] = take ? q : si[q + 1];
+        }
+        int pv = v[0], pi = 0;
 #pragma unroll
         for (int q = 0; q < kBlk; ++q) {
-            const int v = vt[r0 + q][c];
-            const bool take = v > pv;
-            pv = take ? v : pv;
-            pi = take ? r0 + q : pi;
-            pre_v[r0 + q][c] = pv;
-            pre_i[r0 + q][c] = (unsigned char)pi;
+            const bool take = v[q] > pv;
+            pv = take ? v[q] : pv;
+            pi = take ? q : pi;
+            const int o = at(r0, c) + q * COLS;
+            vt[o] = v[q];
+            pre_v[o] = pv;
+            suf_v[o] = sv[q];
+            ps_i[(r0 + q) * COLS + c] = (unsigned char)(pi | (si[q] << 4));
         }
-        int sv = kEmpty, si = r0 + kBlk - 1;
-#pragma unroll
-        for (int q = kBlk - 1; q >= 0; --q) {
-            const int v = vt[r0 + q][c];
-            const bool take = v >= sv;
-            sv = take ? v : sv;
-            si = take ? r0 + q : si;
-            suf_v[r0 + q][c] = sv;
-            suf_i[r0 + q][c] = (unsigned char)si;
-        }
-        run_v[0][rq][c] = sv;
-        run_i[0][rq][c] = (unsigned char)si;
+        run_v[0][rq][c] = sv[0];
+        run_i[0][rq][c] = (unsigned short)(r0 + si[0]);
+    }
+    for (int r = t; r < D; r += C::THREADS) {
+        int lo, hi;
+        window_of(n, a.full, a.win, a.bound, r - (n - 1), lo, hi);
+        wlo[r] = (unsigned short)(lo + n - 1);
+        whi[r] = (unsigned short)(hi + n - 1);
     }
     __syncthreads();
     if (rq < NB) {
-        // runs of 2, 4, 8 blocks from block rq, ascending (ties keep the first)
+        // runs of 2, 4, .. blocks from block rq, ascending (ties keep the first)
         int mv = run_v[0][rq][c], mi = run_i[0][rq][c];
 #pragma unroll
-        for (int l = 1; l < kBlkLevels; ++l) {
-#pragma unroll
+        for (int l = 1; l < LV; ++l) {
+#pragma unroll 8
             for (int b = (1 << (l - 1)); b < (1 << l); ++b) {
                 const int bb = min(rq + b, NB - 1);
                 const int v = run_v[0][bb][c];
+                const int vi = run_i[0][bb][c];
                 const bool take = rq + b < NB && v > mv;
                 mv = take ? v : mv;
-                mi = take ? run_i[0][bb][c] : mi;
+                mi = take ? vi : mi;
             }
             run_v[l][rq][c] = mv;
-            run_i[l][rq][c] = (unsigned char)mi;
+            run_i[l][rq][c] = (unsigned short)mi;
         }
     }
     __syncthreads();
 
     const bool last = a.key != nullptr;  // the image's last step: keys, no planes
-    const RowView ov = row_view(last ? a.vin : a.vout, a.v_pitch, 4, 0, D, D);
-    const RowView av = row_view(last ? a.vin : a.aout, a.a_pitch, sizeof(AT), 0, D, D);
     const bool col = xp < w;
     Best best;
 #pragma unroll
-    for (int j = 0; j < kBlkOut; ++j) {
-        const int r = rq + kBlkLanes * j;
+    for (int j = 0; j < C::OUT; ++j) {
+        const int r = rq + C::LANES * j;
         if (r >= D) break;
         const int lo = wlo[r], hi = whi[r];
         const int bl = lo / kBlk, bh = hi / kBlk;
@@ -1445,52 +1294,44 @@ __global__ __launch_bounds__(kBlkThreads) void dp_step_blocks(DpPack<CAP> pk) {
             m = kEmpty;
             ia = lo;
             for (int q = lo; q <= hi; ++q) {
-                const int v = vt[q][c];
+                const int v = vt[at(q, c)];
                 const bool take = v > m;
                 m = take ? v : m;
                 ia = take ? q : ia;
             }
         } else {
-            m = suf_v[lo][c];
-            ia = suf_i[lo][c];
+            m = suf_v[at(lo, c)];
+            ia = bl * kBlk + (ps_i[lo * COLS + c] >> 4);
             const int cnt = bh - bl - 1;  // whole blocks between
             if (cnt > 0) {
                 const int l = 31 - __builtin_clz((unsigned)cnt);
                 const int v1 = run_v[l][bl + 1][c], v2 = run_v[l][bh - (1 << l)][c];
+                const int i1 = run_i[l][bl + 1][c], i2 = run_i[l][bh - (1 << l)][c];
                 const bool t1 = v1 > m;
                 m = t1 ? v1 : m;
-                ia = t1 ? run_i[l][bl + 1][c] : ia;
+                ia = t1 ? i1 : ia;
                 const bool t2 = v2 > m;
                 m = t2 ? v2 : m;
-                ia = t2 ? run_i[l][bh - (1 << l)][c] : ia;
+                ia = t2 ? i2 : ia;
             }
-            const int vp = pre_v[hi][c];
+            const int vp = pre_v[at(hi, c)];
             const bool tp = vp > m;
             m = tp ? vp : m;
-            ia = tp ? pre_i[hi][c] : ia;
+            ia = tp ? bh * kBlk + (ps_i[hi * COLS + c] & 15) : ia;
         }
         if (!col) continue;
+        const int x = xp - (r - (n - 1));
+        const int val = m >= 0 && (a.out_pin_x < 0 || x == a.out_pin_x) ? hv[j] + m : -1;
         if (last) {
-            const int x = xp - (r - (n - 1));
-            if ((unsigned)x < (unsigned)w) take_best(best, pack_key(m >= 0 ? hv[j] + m : -1, x, r, D), ia);
+            if ((unsigned)x < (unsigned)w) take_best(best, pack_key(val, x, r, D), ia);
             continue;
         }
-        const unsigned int aoff = (unsigned int)r * a.a_pitch * sizeof(AT) + (unsigned int)xp * sizeof(AT);
-        if constexpr (sizeof(AT) == 1)
-            __builtin_amdgcn_raw_buffer_store_b8((unsigned char)ia, av.rs, (int)aoff, 0, kStoreScope);
-        else
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)ia, av.rs, (int)aoff, 0, kStoreScope);
-        const int x = xp - (r - (n - 1));
-        if ((unsigned)x < (unsigned)w) {
-            const int val = m >= 0 ? hv[j] + m : -1;
-            __builtin_amdgcn_raw_buffer_store_b32(
-                val, ov.rs, (int)((unsigned int)r * a.v_pitch * 4u + (unsigned int)x * 4u), 0,
-                kStoreScope);
-        }
+        (static_cast<AT*>(a.aout) + (size_t)r * a.a_pitch)[xp] = (AT)ia;
+        if ((unsigned)x < (unsigned)w) (a.vout + (size_t)r * a.v_pitch)[x] = val;
     }
     if (last) {
         // the workgroup's best key and that cell's successor, slot = column tile
-        constexpr int W = kBlkThreads / 64;
+        constexpr int W = (C::THREADS + 63) / 64;
         __shared__ unsigned long long part[W];
         __shared__ int part_s[W];
         const int lane = t & 63, wave = t >> 6;
@@ -2178,11 +2019,13 @@ struct DpClass {
     int dc;     // fixed kernels: displacements per thread
     bool a16;
     bool narrow;  // uint16 tables (bands 0 .. k-2)
+    int rows;     // scanned windows: rows of the block kernel's tile, else 0
+    int cols = 0; // and its columns (per launch)
     int steps;    // most DP steps per launch allowed, 1..3 (tuning)
     int stripe;   // item-order stripe of the multi-step kernels (tuning)
     bool operator==(const DpClass& o) const {
         return kind == o.kind && bound == o.bound && dc == o.dc && a16 == o.a16 &&
-               narrow == o.narrow && steps == o.steps && stripe == o.stripe;
+               narrow == o.narrow && rows == o.rows && steps == o.steps && stripe == o.stripe;
     }
 };
 
@@ -2205,6 +2048,35 @@ bool colmax_apply(const DpJobSpec& J) {
     return J.plan.kind == WindowKind::Full && J.pin.j < 0 && J.g.k >= 2 && J.g.D >= 3;
 }
 
+// Tile of the block kernel: the rows it holds (D < rows).
+int blk_rows(const Geometry& g) {
+    int r = 64;
+    while (r <= g.D) r *= 2;
+    return r;
+}
+
+// Its most columns (what LDS holds; 32 columns of 255 rows were slower at every
+// width), and its columns in a launch of one image: the fewest that need at most
+// one workgroup per CU.  A narrower tile shortens every phase of a launch while
+// CUs are idle; with more than one workgroup a CU the wider row segments win.
+// Detections of 128-row bands, k = 16, 0.1 rad, 4 / 8 / 16 columns: w = 300 93 /
+// 101 / 120 us, 1500 112 / 103 / 121, 3000 158 / 129 / 129, 8000 307 / 232 / 197;
+// 511 displacements at w = 2047 101 / 94 / 114.  A pack of images keeps the most.
+// The last step writes a key per tile and takes the fewest columns whose keys fit.
+constexpr int blk_most_cols(int rows) {
+    return rows <= 512 ? 16 : rows == 1024 ? 8 : 4;
+}
+int blk_cols(const Geometry& g, bool alone, bool last) {
+    constexpr int kCus = 256;  // compute units of the MI355X
+    const int most = blk_most_cols(blk_rows(g));
+    int c = most;
+    if (alone)
+        for (c = 4; c < most && (g.w + c - 1) / c > kCus;) c *= 2;
+    if (last)
+        while ((size_t)((g.w + c - 1) / c) > dp_key_count(g)) c *= 2;
+    return c < most ? c : most;
+}
+
 DpClass class_of(const DpJobSpec& j) {
     DpClass c;
     c.kind = (int)j.plan.kind;
@@ -2215,16 +2087,19 @@ DpClass class_of(const DpJobSpec& j) {
     c.narrow = j.tables.narrow > 0;
     c.steps = j.plan.steps;
     c.stripe = j.plan.stripe;
-    if (j.plan.kind == WindowKind::Full && colmax_apply(j))
+    c.rows = 0;
+    if (j.plan.kind == WindowKind::Full && colmax_apply(j)) {
         c.kind = (int)WindowKind::Full;  // the column recurrence
-    else if (!fixed)
-        c.kind = (int)WindowKind::Generic;  // one scanning kernel for every other kind
+    } else if (!fixed) {
+        c.kind = (int)WindowKind::Generic;  // the block kernel for every other kind
+        c.rows = blk_rows(j.g);
+    }
     return c;
 }
 
 // Kernel family of a class's single-step launches (for the timing brackets).
 const char* step_family(const DpClass& c) {
-    return c.kind == (int)WindowKind::Fixed ? "dp_step_fixed" : "dp_step_generic";
+    return c.kind == (int)WindowKind::Fixed ? "dp_step_fixed" : "dp_step_blocks";
 }
 
 int items_y_of(const Geometry& g, int dc) {
@@ -2245,9 +2120,39 @@ void launch_fixed_b(int dc, hipStream_t s, const DpPack<CAP>& pk) {
 template <typename AT, int CAP, typename TT>
 hipError_t launch_step_t(const DpClass& c, hipStream_t s, const DpPack<CAP>& pk) {
     if (c.kind != (int)WindowKind::Fixed) {
-        hipLaunchKernelGGL((dp_step_generic<AT, CAP, TT>), dim3(pk.total), dim3(64 * kWaves), 0, s,
-                           pk);
-        return hipSuccess;
+        auto blocks = [&](auto rows_tag) {
+            constexpr int ROWS = decltype(rows_tag)::value;
+            auto tile = [&](auto cols_tag) {
+                constexpr int COLS = decltype(cols_tag)::value;
+                if constexpr (COLS <= blk_most_cols(ROWS))
+                    hipLaunchKernelGGL((dp_step_blocks<ROWS, COLS, AT, CAP, TT>), dim3(pk.total),
+                                       dim3(BlkCfg<ROWS, COLS>::THREADS), 0, s, pk);
+            };
+            if constexpr (CAP > 1) {
+                tile(std::integral_constant<int, blk_most_cols(ROWS)>{});
+            } else {
+                switch (c.cols) {
+                    case 4: tile(std::integral_constant<int, 4>{}); break;
+                    case 8: tile(std::integral_constant<int, 8>{}); break;
+                    default: tile(std::integral_constant<int, 16>{}); break;
+                }
+            }
+        };
+        if constexpr (sizeof(AT) == 1) {  // at most 256 displacements
+            switch (c.rows) {
+                case 64: blocks(std::integral_constant<int, 64>{}); return hipSuccess;
+                case 128: blocks(std::integral_constant<int, 128>{}); return hipSuccess;
+                case 256: blocks(std::integral_constant<int, 256>{}); return hipSuccess;
+                default: return hipErrorInvalidValue;
+            }
+        } else {
+            switch (c.rows) {
+                case 512: blocks(std::integral_constant<int, 512>{}); return hipSuccess;
+                case 1024: blocks(std::integral_constant<int, 1024>{}); return hipSuccess;
+                case 2048: blocks(std::integral_constant<int, 2048>{}); return hipSuccess;
+                default: return hipErrorInvalidValue;
+            }
+        }
     }
 #define FHTP_B(BB) \
     case BB: launch_fixed_b<BB, AT, CAP, TT>(c.dc, s, pk); return hipSuccess;
@@ -2289,47 +2194,17 @@ DpJob base_job(const DpJobSpec& J) {
     return a;
 }
 
-// The block kernel takes scanned windows (the angle form, bounds above the
-// fixed-window kernels') of bands with at most 255 displacements, without a
-// through-point pin.
-bool blocks_apply(const DpJobSpec& J) {
-    return (J.plan.kind == WindowKind::Angle || J.plan.kind == WindowKind::Generic) &&
-           J.pin.j < 0 && J.g.D <= kBlkRows - 1;
-}
-
 // Steps of a pack of images of one class (each with k >= 2).
 template <typename AT, int CAP>
 hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs, hipStream_t s) {
     int max_steps = 0;
     for (const DpJobSpec* J : jobs) max_steps = std::max(max_steps, J->g.k - 1);
-    // Steps that take the block kernel and the others, each run of launches
-    // of one kernel in one timing bracket.
-    auto blocks_at = [&](const DpJobSpec& J, int) { return blocks_apply(J); };
-    std::vector<const char*> seq;  // kernel family of every launch, in order
+    TimedLaunch tl(step_family(c), s, max_steps);  // one bracket around the run of launches
     for (int st = 0; st < max_steps; ++st) {
-        bool b = false, o = false;
-        for (const DpJobSpec* J : jobs) {
-            if (J->g.k - 1 <= st) continue;
-            (blocks_at(*J, st) ? b : o) = true;
-        }
-        if (b) seq.push_back("dp_step_blocks");
-        if (o) seq.push_back(step_family(c));
-    }
-    std::unique_ptr<TimedLaunch> tl;
-    size_t q = 0;
-    auto bracket = [&]() {  // before launch q: a bracket per run of one family
-        if (q == 0 || seq[q] != seq[q - 1]) {
-            tl.reset();
-            size_t e = q;
-            while (e < seq.size() && seq[e] == seq[q]) ++e;
-            tl.reset(new TimedLaunch(seq[q], s, (int)(e - q)));
-        }
-        ++q;
-    };
-    for (int st = 0; st < max_steps; ++st) {
-        DpPack<CAP> pk{}, pb{};
-        long long total = 0, tb = 0;
-        int cnt = 0, cb = 0;
+        DpPack<CAP> pk{};
+        DpClass cs = c;  // with the launch's columns
+        long long total = 0;
+        int cnt = 0;
         for (const DpJobSpec* J : jobs) {
             const Geometry& g = J->g;
             if (g.k - 1 <= st) continue;
@@ -2349,41 +2224,23 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
             a.succ = last ? J->buf.succ : nullptr;
             if (st == 0) first_step_pin(*J, a.vin_pin, a.vin_pin_x);
             a.out_pin_x = J->pin.j == i ? J->pin.x : -1;
-            if (blocks_at(*J, st)) {
-                a.items_x = (g.w + kBlkCols - 1) / kBlkCols;
+            if (c.rows) {
+                cs.cols = blk_cols(g, CAP == 1, last);
+                a.items_x = (g.w + cs.cols - 1) / cs.cols;
                 a.items_y = 1;
-                a.item0 = (int)tb;
-                tb += a.items_x;
-                if (tb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-                pb.job[cb++] = a;
-                continue;
+            } else {
+                a.items_y = items_y_of(g, c.dc);
             }
-            a.items_y = items_y_of(g, c.dc);
             a.item0 = (int)total;
             total += (long long)a.items_x * a.items_y;
             if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
             pk.job[cnt++] = a;
         }
-        if (cb > 0) {
-            pb.count = cb;
-            pb.total = (int)tb;
-            bracket();
-            if (c.narrow)
-                hipLaunchKernelGGL((dp_step_blocks<AT, CAP, uint16_t>), dim3((unsigned)tb),
-                                   dim3(kBlkThreads), 0, s, pb);
-            else
-                hipLaunchKernelGGL((dp_step_blocks<AT, CAP, int32_t>), dim3((unsigned)tb),
-                                   dim3(kBlkThreads), 0, s, pb);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        if (cnt > 0) {
-            pk.count = cnt;
-            pk.total = (int)total;
-            bracket();
-            hipError_t e = launch_step<AT, CAP>(c, s, pk);
-            if (e != hipSuccess) return e;
-        }
+        pk.count = cnt;
+        pk.total = (int)total;
+        hipError_t e = launch_step<AT, CAP>(cs, s, pk);
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -2754,8 +2611,8 @@ hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs,
             a.key = J.buf.key;
             a.succ = J.buf.succ;
             a.n_keys = g.k == 1        ? (int)(((g.w + 63) / 64) * items_y_of(g, kDCGeneric))
-                       : blocks_apply(J) ? (g.w + kBlkCols - 1) / kBlkCols  // one per column tile
-                                         : (int)(((g.w + 63) / 64) * items_y_of(g, c.dc));
+                       : c.rows ? (g.w + blk_cols(g, CAP == 1, true) - 1) / blk_cols(g, CAP == 1, true)
+                                : (int)(((g.w + 63) / 64) * items_y_of(g, c.dc));
             a.a_base = J.buf.a;
             a.a_plane = (size_t)g.D * g.pitch;
             a.a_pitch = g.pitch;
@@ -2875,9 +2732,9 @@ size_t dp_plane_bytes(const Geometry& g) { return (size_t)g.D * g.pitch * sizeof
 size_t dp_key_count(const Geometry& g) {
     // workgroups of the last step: at 8 displacements per thread (the
     // largest grid of the 64-column kernels), or one per column tile of the
-    // block kernel
+    // block kernel (16 columns; 8 or 4 only for bands whose first count is larger)
     const size_t k64 = (size_t)((g.w + 63) / 64) * items_y_of(g, 8);
-    const size_t k16 = (size_t)((g.w + kBlkCols - 1) / kBlkCols);
+    const size_t k16 = (size_t)((g.w + 15) / 16);
     return k64 > k16 ? k64 : k16;
 }
 
