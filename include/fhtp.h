@@ -310,7 +310,7 @@ int fhtp_plan_destroy(fhtp_plan plan);
  *             library's choice, 2); two and three need dc 8 (or 0), three a
  *             bound of at most 8 shifts and no through-point pin (else two);
  *   stripe:   column tiles per stripe of the multi-step kernels' workgroup
- *             order, 1..64 (0: 16);
+ *             order, 1..64 (0: the library's choice by width, 16..32);
  *   fht_grid: of short bands (at most 16 rows of 8-bit pixels, 32 of 16-bit
  *             ones), 0: the FHT's resident grid loops over the work items; 1:
  *             one workgroup per work item (as taller bands always run);

@@ -59,12 +59,26 @@ int pixels(fhtp_dtype dtype, int h) {
     return FHTP_OK;
 }
 
-// Displacements per thread of the fixed-window DP step: 8 gives twice the
-// waves of 16 at the cost of more halo loads (from cache), which pays until
-// the grid fills the chip twice over.
+// Displacements per thread of the fixed-window DP step.  8, which also lets
+// steps run two per launch (images of at least four bands); with fewer bands,
+// where every launch is one step, 16 once the grid fills the chip twice over
+// (half the waves, fewer halo loads).  Large grids took 16 and one step per
+// launch before: 16384 x 16384, k = 128, bound 8 1963 us of steps against 1400,
+// 4096 x 8192, k = 32 251 against 170.
 int dp_chunk(const fhtp::Geometry& g) {
+    if (g.k >= 4) return 8;
     const long long threads16 = (long long)g.w * ((g.D + 15) / 16);
     return threads16 < 256LL * 4 * 64 * 2 ? 8 : 16;
+}
+
+// Column tiles (of 64) per stripe of the multi-step kernels' workgroup order:
+// an XCD's eighth of the tiles, so that its run of workgroups is one block of
+// the plane, within [16, 32].  Pair launches at 16384 columns, k = 128: stripes
+// of 8 / 16 / 32 / 64 tiles 1472 / 1432 / 1380 / 1486 us; at 8192, k = 32 175 /
+// 170 / 174 / 181.
+int dp_stripe(const fhtp::Geometry& g) {
+    const int eighth = (g.w + 511) / 512;
+    return eighth < 16 ? 16 : eighth < 32 ? eighth : 32;
 }
 
 // ---- tuning rules (fhtp_tune_set) ----------------------------------------------
@@ -96,7 +110,7 @@ void apply_tuning(const fhtp::Geometry& g, int dtype, fhtp::DpPlan* pl) {
         if (r.window != -1 && r.window != window) continue;
         if (r.dc) pl->dc = r.dc;
         if (r.steps) pl->steps = r.steps;
-        pl->stripe = r.stripe ? r.stripe : 16;
+        if (r.stripe) pl->stripe = r.stripe;
         pl->fht_grid = r.fht_grid;
         pl->small = r.small == 0;
         return;
@@ -108,7 +122,7 @@ int plan_window(const fhtp::Geometry& g, fhtp_bend b, fhtp::DpPlan* pl) {
     pl->a16 = g.D > 256;
     pl->dc = dp_chunk(g);
     pl->steps = 2;
-    pl->stripe = 16;
+    pl->stripe = dp_stripe(g);
     pl->fht_grid = 0;
     pl->small = true;
     pl->bound = 0;
