@@ -1793,9 +1793,13 @@ __global__ __launch_bounds__(64) void angle_windows(int n, double t, int32_t* __
 // d_i = B_i(x_i).  The greedy smallest index at every step gives the
 // lexicographically smallest optimal polyline, as in the other kernels.
 //
-// Layout: a workgroup owns 64 columns x (one per lane, coalesced loads) and
-// its kColWaves waves split the displacement rows, each scanning its rows in
-// ascending order; the waves' partial maxima meet in LDS, lowest rows first.
+// Layout: a workgroup owns COLS columns x and every displacement row; its
+// threads take a column and a run of rows each, ascending, and their partial
+// maxima meet first in the wave, then in LDS (larger values win, the smaller row
+// where equal).  Bound by the chain of a launch (its loads are one round trip
+// where a thread has at most 8 rows): 3.6 us at 1501 columns of 255 displacements,
+// 4.5 with 64 columns a workgroup, of which a chip then has 24.  Rows dealt out
+// one by one instead of in runs: 82.0 against 73.6 us a detection.
 constexpr int kColWaves = 16;
 
 struct ColJob {
@@ -1820,8 +1824,9 @@ __device__ __forceinline__ unsigned long long col_key(int val, int x) {
            (unsigned long long)(0xffffffffu - (unsigned int)x);
 }
 
-template <typename AT, int CAP, typename TT>
+template <int COLS, typename AT, int CAP, typename TT>
 __global__ __launch_bounds__(64 * kColWaves) void dp_colmax(ColPack<CAP> pk) {
+    constexpr int LANES = 64 * kColWaves / COLS;  // row lanes
     const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     int jj = 0;
     if constexpr (CAP > 1) {
@@ -1839,52 +1844,77 @@ __global__ __launch_bounds__(64 * kColWaves) void dp_colmax(ColPack<CAP> pk) {
     const int tile = CAP > 1 ? it - a.item0 : it;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int x = tile * 64 + lane;
+    const int c = threadIdx.x % COLS;
+    const int x = tile * COLS + c;
     const bool col = x < w;
-    const int R = (D + kColWaves - 1) / kColWaves;
-    const int r0 = wave * R, r1 = min(r0 + R, D);
     const TT* H = static_cast<const TT*>(a.htab);
     int best = kEmpty, brow = 0;
-    for (int rb = r0; rb < r1; rb += 8) {
-        int hv[8], uv[8];
-        bool ok[8];
+    const int R = (D + LANES - 1) / LANES;  // rows of a thread
+    const int r0 = threadIdx.x / COLS * R, r1 = min(r0 + R, D);
+    auto rows = [&](auto u_tag) {  // U rows in flight at once
+        constexpr int U = decltype(u_tag)::value;
+        for (int rb = r0; rb < r1; rb += U) {
+            int hv[U], uv[U];
+            bool ok[U];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int r = rb + j;
-            const int xt = x + r - (n - 1);  // successor column x + d
-            ok[j] = col && r < r1 && (unsigned)xt < (unsigned)w;
-            const size_t off = ok[j] ? (size_t)r * (size_t)a.h_pitch + (size_t)x : 0;
-            hv[j] = (int)H[off];
-            uv[j] = a.uin ? a.uin[ok[j] ? xt : 0] : 0;
-        }
+            for (int j = 0; j < U; ++j) {
+                const int r = rb + j;
+                const int xt = x + r - (n - 1);  // successor column x + d
+                ok[j] = col && r < r1 && (unsigned)xt < (unsigned)w;
+                const size_t off = ok[j] ? (size_t)r * (size_t)a.h_pitch + (size_t)x : 0;
+                hv[j] = (int)H[off];
+                uv[j] = a.uin ? a.uin[ok[j] ? xt : 0] : 0;
+            }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int v = hv[j] + uv[j];
-            const bool t = ok[j] && v > best;  // ascending rows: ties keep the smaller d
-            best = t ? v : best;
-            brow = t ? rb + j : brow;
+            for (int j = 0; j < U; ++j) {
+                const int v = hv[j] + uv[j];
+                const bool t = ok[j] && v > best;  // ascending rows: ties keep the smaller d
+                best = t ? v : best;
+                brow = t ? rb + j : brow;
+            }
         }
+    };
+    if (D <= LANES)
+        rows(std::integral_constant<int, 1>{});
+    else if (D <= 2 * LANES)
+        rows(std::integral_constant<int, 2>{});
+    else if (D <= 4 * LANES)
+        rows(std::integral_constant<int, 4>{});
+    else
+        rows(std::integral_constant<int, 8>{});
+    auto take = [&](int v, int r) {
+        const bool t = v > best || (v == best && r < brow);
+        best = t ? v : best;
+        brow = t ? r : brow;
+    };
+#pragma unroll
+    for (int o = COLS; o < 64; o *= 2) {  // the wave's row lanes
+        const int v = __shfl_xor(best, o, 64), r = __shfl_xor(brow, o, 64);
+        take(v, r);
     }
-    __shared__ int pv[kColWaves][64];
-    __shared__ int pr[kColWaves][64];
-    pv[wave][lane] = best;
-    pr[wave][lane] = brow;
+    __shared__ int pv[kColWaves][COLS];
+    __shared__ int pr[kColWaves][COLS];
+    if (lane < COLS) {
+        pv[wave][c] = best;
+        pr[wave][c] = brow;
+    }
     __syncthreads();
     if (wave != 0) return;
-    // waves hold ascending row ranges: a later wave wins only when larger
-    int b = pv[0][lane], r = pr[0][lane];
+    if (lane < COLS) {
+        // waves hold ascending row ranges: a later wave wins only when larger
 #pragma unroll
-    for (int q = 1; q < kColWaves; ++q) {
-        const bool t = pv[q][lane] > b;
-        b = t ? pv[q][lane] : b;
-        r = t ? pr[q][lane] : r;
-    }
-    if (col) {
-        static_cast<AT*>(a.bout)[x] = (AT)r;
-        if (a.uout) a.uout[x] = b;
+        for (int q = 1; q < kColWaves; ++q) {
+            const bool t = pv[q][c] > best;
+            best = t ? pv[q][c] : best;
+            brow = t ? pr[q][c] : brow;
+        }
+        if (col) {
+            static_cast<AT*>(a.bout)[x] = (AT)brow;
+            if (a.uout) a.uout[x] = best;
+        }
     }
     if (a.key) {
-        const unsigned long long kk = wave_max_u64(col ? col_key(b, x) : 0ull);
+        const unsigned long long kk = wave_max_u64(lane < COLS && col ? col_key(best, x) : 0ull);
         if (lane == 0) a.key[tile] = kk;
     }
 }
@@ -2517,6 +2547,22 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
     return launch_step<AT, CAP>(c, s, pk);
 }
 
+// Columns of a workgroup of the column recurrence: as blk_cols, the fewest that
+// need at most one workgroup per CU, at most 32.  Detections without a bend
+// limit, 8 / 16 / 32 / 64 columns: 2048 x 1501, k = 16 73.6 / 73.8 / 78.7 / 94.8 us;
+// 4096 x 4096, k = 32 194 / 180 / 185 / 220; 2048 x 8000, k = 16 146 / 106 / 101 /
+// 118.  A pack of images keeps 32.  The last step writes a key per tile and takes
+// the fewest columns whose keys fit.
+int col_cols(const Geometry& g, bool alone, bool last) {
+    constexpr int kCus = 256;
+    int c = 32;
+    if (alone)
+        for (c = 8; c < 32 && (g.w + c - 1) / c > kCus;) c *= 2;
+    if (last)
+        while (c < 32 && (size_t)((g.w + c - 1) / c) > dp_key_count(g)) c *= 2;
+    return c;
+}
+
 // Steps of the column recurrence for a pack of images: launch L makes band
 // Q-1-L of every image with more bands than that (Q: the most bands), so
 // every image's band 0 is in the final launch.  U_i goes to row 0 of value
@@ -2533,7 +2579,7 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
         for (int wide = 1; wide >= 0; --wide) {
             ColPack<CAP> pk{};
             long long total = 0;
-            int cnt = 0;
+            int cnt = 0, cols = 32;
             for (const DpJobSpec* J : jobs) {
                 const Geometry& g = J->g;
                 if (g.k <= i) continue;
@@ -2550,17 +2596,30 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
                 a.n = g.n;
                 a.w = g.w;
                 a.item0 = (int)total;
-                total += (g.w + 63) / 64;
+                cols = col_cols(g, CAP == 1, i == 0);
+                total += (g.w + cols - 1) / cols;
                 if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
                 pk.job[cnt++] = a;
             }
             if (cnt == 0) continue;
             pk.count = cnt;
             const dim3 grid((unsigned)total), block(64 * kColWaves);
-            if (!wide && c.narrow)
-                hipLaunchKernelGGL((dp_colmax<AT, CAP, uint16_t>), grid, block, 0, s, pk);
-            else
-                hipLaunchKernelGGL((dp_colmax<AT, CAP, int32_t>), grid, block, 0, s, pk);
+            auto launch = [&](auto cols_tag) {
+                constexpr int COLS = decltype(cols_tag)::value;
+                if (!wide && c.narrow)
+                    hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, uint16_t>), grid, block, 0, s, pk);
+                else
+                    hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, int32_t>), grid, block, 0, s, pk);
+            };
+            if constexpr (CAP > 1) {
+                launch(std::integral_constant<int, 32>{});
+            } else {
+                switch (cols) {
+                    case 8: launch(std::integral_constant<int, 8>{}); break;
+                    case 16: launch(std::integral_constant<int, 16>{}); break;
+                    default: launch(std::integral_constant<int, 32>{}); break;
+                }
+            }
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -2581,7 +2640,8 @@ hipError_t run_colmax_walks(const std::vector<const DpJobSpec*>& jobs, hipStream
             a.score = J.score;
             a.xs = J.xs;
             a.b_pitch = J.g.pitch;
-            a.n_keys = (J.g.w + 63) / 64;
+            const int cols = col_cols(J.g, CAP == 1, true);
+            a.n_keys = (J.g.w + cols - 1) / cols;
             a.n = J.g.n;
             a.w = J.g.w;
             a.k = J.g.k;
