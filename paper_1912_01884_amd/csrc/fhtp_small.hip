@@ -38,6 +38,7 @@ namespace {
 constexpr int kSmallThreads = 1024;  // 16 waves on the workgroup's CU
 constexpr int kSmallMaxN = 32;
 constexpr size_t kSmallLds = 64 * 1024;
+constexpr size_t kSmallOneLds = 128 * 1024;  // one image alone on its CU
 constexpr int kSmallPack = 256;  // images per launch
 
 struct SmallJob {
@@ -66,10 +67,112 @@ size_t small_lds_bytes(int n, int w, int k, int bpp) {
            align4((size_t)(k > 1 ? k - 1 : 0) * D * w) + 2 * D * 4;
 }
 
+// Of one image alone (detect_small_one): no table, but every band's 4-row sums.
+// At most 120 KB for the images that take it (small_apply).
+size_t small_one_lds_bytes(int n, int w, int k, int bpp) {
+    const size_t D = 2 * (size_t)n - 1;
+    return small_lds_bytes(n, w, k, bpp) - D * w * 4 + (n >= 8 ? 7 * (size_t)(n / 4) * k * w * 4 : 0);
+}
+
 __device__ __forceinline__ unsigned long long small_key(int val, int x, int r, int D) {
     const unsigned int lin = (unsigned int)x * (unsigned int)D + (unsigned int)r;
     return ((unsigned long long)(unsigned int)(val + 1) << 32) |
            (unsigned long long)(0xffffffffu - lin);
+}
+
+// The image, once: 16-byte loads when the source is aligned, four in flight per
+// thread, then the bytes left over.
+__device__ __forceinline__ void small_load_image(const char* src, char* dst, int bytes) {
+    const int t = threadIdx.x;
+    int done = 0;
+    if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+        const int n16 = bytes / 16;
+        const uint4* s16 = reinterpret_cast<const uint4*>(src);
+        uint4* d16 = reinterpret_cast<uint4*>(dst);
+        for (int q0 = t; q0 < n16; q0 += 4 * kSmallThreads) {
+            uint4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = q0 + u * kSmallThreads;
+                v[u] = s16[q < n16 ? q : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = q0 + u * kSmallThreads;
+                if (q < n16) d16[q] = v[u];
+            }
+        }
+        done = n16 * 16;
+    }
+    for (int q0 = done + t; q0 < bytes; q0 += 4 * kSmallThreads) {
+        char v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = q0 + u * kSmallThreads;
+            v[u] = src[q < bytes ? q : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = q0 + u * kSmallThreads;
+            if (q < bytes) dst[q] = v[u];
+        }
+    }
+}
+
+// Admissible successor rows [lo, hi] of displacement d.
+template <int n, int D>
+__device__ __forceinline__ void small_window(int kind, int bound, double tan_g, int d, int& lo,
+                                             int& hi) {
+    if (kind == (int)WindowKind::Angle) {
+        lo = D;
+        hi = -1;
+        for (int rp = 0; rp < D; ++rp) {
+            const int dp = rp - (n - 1);
+            const double lhs = (double)n * (double)abs(dp - d);
+            const double rhs = tan_g * ((double)n * (double)n + (double)d * (double)dp);
+            if (lhs <= rhs) {
+                lo = min(lo, rp);
+                hi = max(hi, rp);
+            }
+        }
+    } else if (kind == (int)WindowKind::Full) {
+        lo = 0;
+        hi = D - 1;
+    } else {
+        lo = max(d - bound, -(n - 1)) + n - 1;
+        hi = min(d + bound, n - 1) + n - 1;
+    }
+}
+
+// The best key of the workgroup (wave maxima, then one thread) and the walk from
+// it along the back-pointers A.
+template <int n, int D>
+__device__ __forceinline__ void small_finish(const SmallJob& a, unsigned long long best,
+                                             unsigned long long* part, const unsigned char* A) {
+    const int w = a.w, k = a.k, cells = D * w, t = threadIdx.x;
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned long long v = __shfl_xor(best, o, 64);
+        best = v > best ? v : best;
+    }
+    if ((t & 63) == 0) part[t >> 6] = best;
+    __syncthreads();
+    if (t != 0) return;
+    unsigned long long kv = part[0];
+    for (int q = 1; q < kSmallThreads / 64; ++q) kv = part[q] > kv ? part[q] : kv;
+    const unsigned int lin = 0xffffffffu - (unsigned int)(kv & 0xffffffffull);
+    if ((kv >> 32) == 0 || lin / (unsigned int)D >= (unsigned int)w) {
+        *a.score = -1;
+        return;
+    }
+    int x = (int)(lin / (unsigned int)D), r = (int)(lin % (unsigned int)D);
+    a.xs[0] = x;
+    for (int i = 0; i + 1 < k; ++i) {
+        x += r - (n - 1);  // x_{i+1}
+        a.xs[i + 1] = x;
+        r = A[(size_t)i * cells + (size_t)r * w + x];
+    }
+    a.xs[k] = x + r - (n - 1);
+    *a.score = (int)(kv >> 32) - 1;
 }
 
 // N: the band height (a compile-time constant, so that a line's N reads are
@@ -99,69 +202,13 @@ __global__ __launch_bounds__(kSmallThreads) void detect_small(SmallPack<CAP> pk)
     int* wlo = reinterpret_cast<int*>(base);
     int* whi = wlo + D;
 
-    // the image, once: 16-byte loads when the source is aligned, four in
-    // flight per thread, then the bytes left over
-    {
-        const int bytes = n * k * w * (int)sizeof(PixT);
-        const char* src = static_cast<const char*>(a.img);
-        char* dst = reinterpret_cast<char*>(img);
-        int done = 0;
-        if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-            const int n16 = bytes / 16;
-            const uint4* s16 = reinterpret_cast<const uint4*>(src);
-            uint4* d16 = reinterpret_cast<uint4*>(dst);
-            for (int q0 = t; q0 < n16; q0 += 4 * kSmallThreads) {
-                uint4 v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int q = q0 + u * kSmallThreads;
-                    v[u] = s16[q < n16 ? q : 0];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int q = q0 + u * kSmallThreads;
-                    if (q < n16) d16[q] = v[u];
-                }
-            }
-            done = n16 * 16;
-        }
-        for (int q0 = done + t; q0 < bytes; q0 += 4 * kSmallThreads) {
-            char v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + u * kSmallThreads;
-                v[u] = src[q < bytes ? q : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + u * kSmallThreads;
-                if (q < bytes) dst[q] = v[u];
-            }
-        }
-    }
+    small_load_image(static_cast<const char*>(a.img), reinterpret_cast<char*>(img),
+                     n * k * w * (int)sizeof(PixT));
     // windows [lo, hi] of every displacement, as rows
     for (int r = t; r < D; r += kSmallThreads) {
         const int d = r - (n - 1);
         int lo, hi;
-        if (a.kind == (int)WindowKind::Angle) {
-            lo = D;
-            hi = -1;
-            for (int rp = 0; rp < D; ++rp) {
-                const int dp = rp - (n - 1);
-                const double lhs = (double)n * (double)abs(dp - d);
-                const double rhs = a.tan_g * ((double)n * (double)n + (double)d * (double)dp);
-                if (lhs <= rhs) {
-                    lo = min(lo, rp);
-                    hi = max(hi, rp);
-                }
-            }
-        } else if (a.kind == (int)WindowKind::Full) {
-            lo = 0;
-            hi = D - 1;
-        } else {
-            lo = max(d - a.bound, -(n - 1)) + n - 1;
-            hi = min(d + a.bound, n - 1) + n - 1;
-        }
+        small_window<n, D>(a.kind, a.bound, a.tan_g, d, lo, hi);
         wlo[r] = lo;
         whi[r] = hi;
     }
@@ -314,71 +361,231 @@ __global__ __launch_bounds__(kSmallThreads) void detect_small(SmallPack<CAP> pk)
         Vp = Vc;
         Vc = tmp;
     }
-    // the best key of the workgroup: wave maxima, then one thread
-    for (int o = 32; o >= 1; o >>= 1) {
-        const unsigned long long v = __shfl_xor(best, o, 64);
-        best = v > best ? v : best;
-    }
-    if ((t & 63) == 0) part[t >> 6] = best;
+    small_finish<n, D>(a, best, part, A);
+}
+
+// One image alone: as detect_small, but bound by the chain of its phases on one
+// CU, so with as few of them as the recurrence allows.  The 4-row sums of every
+// band come in one phase, a wave per block of 4 rows and 16 pixel reads for its 7
+// lines (they share pixels); the line sums are formed inside the DP step; a band
+// is then one phase and one barrier.  64 x 64, k = 4, bound 1: 9.2 us a detection
+// against 11.4 with a phase of its own for every band's 4-row sums and line sums.
+template <typename PixT, int N>
+__global__ __launch_bounds__(kSmallThreads) void detect_small_one(SmallJob a) {
+    extern __shared__ unsigned long long small_lds[];
+    constexpr int n = N, D = 2 * N - 1;
+    constexpr int p = N >= 32 ? 5 : N >= 16 ? 4 : N >= 8 ? 3 : N >= 4 ? 2 : N >= 2 ? 1 : 0;
+    constexpr bool BLOCKS = N >= 8;  // line sums from 4-row sums
+    constexpr int NB4 = BLOCKS ? N / 4 : 1;
+    constexpr int kRowLanes = kSmallThreads / 64;
+    constexpr int kRowsPer = (D + kRowLanes - 1) / kRowLanes;
+    const int w = a.w, k = a.k, t = threadIdx.x, cells = D * w;
+    const int cx = t & 63, ry = __builtin_amdgcn_readfirstlane(t >> 6);
+    unsigned long long* part = small_lds;
+    char* base = reinterpret_cast<char*>(small_lds + kSmallThreads / 64);
+    PixT* img = reinterpret_cast<PixT*>(base);
+    base += align4((size_t)n * k * w * sizeof(PixT));
+    int* P = reinterpret_cast<int*>(base);  // [4-row block][7 lines][w]
+    int* Vp = P + (BLOCKS ? 7 * NB4 * k * w : 0);
+    int* Vc = Vp + cells;
+    unsigned char* A = reinterpret_cast<unsigned char*>(Vc + cells);
+    int* wlo = reinterpret_cast<int*>(A + align4((size_t)(k > 1 ? k - 1 : 0) * cells));
+    int* whi = wlo + D;
+
+    small_load_image(static_cast<const char*>(a.img), reinterpret_cast<char*>(img),
+                     n * k * w * (int)sizeof(PixT));
+    const bool angle = a.kind == (int)WindowKind::Angle;  // its windows take a loop each
+    if (angle)
+        for (int r = t; r < D; r += kSmallThreads)
+            small_window<n, D>(a.kind, a.bound, a.tan_g, r - (n - 1), wlo[r], whi[r]);
     __syncthreads();
-    if (t != 0) return;
-    unsigned long long kv = part[0];
-    for (int q = 1; q < kSmallThreads / 64; ++q) kv = part[q] > kv ? part[q] : kv;
-    const unsigned int lin = 0xffffffffu - (unsigned int)(kv & 0xffffffffull);
-    if ((kv >> 32) == 0 || lin / (unsigned int)D >= (unsigned int)w) {
-        *a.score = -1;
-        return;
+    // the windows of the wave's rows ry, ry + kRowLanes, ...
+    int wl[kRowsPer], wh[kRowsPer];
+#pragma unroll
+    for (int q = 0; q < kRowsPer; ++q) {
+        const int r = ry + q * kRowLanes;
+        wl[q] = 0;
+        wh[q] = -1;
+        if (r < D) {
+            if (angle) {
+                wl[q] = __builtin_amdgcn_readfirstlane(wlo[r]);
+                wh[q] = __builtin_amdgcn_readfirstlane(whi[r]);
+            } else {
+                small_window<n, D>(a.kind == (int)WindowKind::Full ? a.kind : (int)WindowKind::Fixed,
+                                   a.bound, 0.0, r - (n - 1), wl[q], wh[q]);
+            }
+        }
     }
-    int x = (int)(lin / (unsigned int)D), r = (int)(lin % (unsigned int)D);
-    a.xs[0] = x;
-    for (int i = 0; i + 1 < k; ++i) {
-        x += r - (n - 1);  // x_{i+1}
-        a.xs[i + 1] = x;
-        r = A[(size_t)i * cells + (size_t)r * w + x];
+    if constexpr (BLOCKS) {
+        // The lines of shift 0 .. 3 over rows 4m .. 4m + 3 are at columns x + (0, 0,
+        // 0, 0), (0, 0, 1, 1), (0, 1, 1, 2) and (0, 1, 2, 3), mirrored leaning left
+        // (lines 4 .. 6: shifts 1 .. 3).  Columns past a row's end hold what lies
+        // there (the neighbouring rows, at the end the sums): such sums are
+        // never used.
+        for (int m = ry; m < NB4 * k; m += kRowLanes) {
+            for (int x = cx; x < w; x += 64) {
+                const PixT* r0 = img + (size_t)(4 * m) * w + x;
+                const PixT *r1 = r0 + w, *r2 = r1 + w, *r3 = r2 + w;
+                int b[3], c[5], e[7];
+                const int a0 = (int)r0[0];
+#pragma unroll
+                for (int o = 0; o < 3; ++o) b[o] = (int)r1[o - 1];
+#pragma unroll
+                for (int o = 0; o < 5; ++o) c[o] = (int)r2[o - 2];
+#pragma unroll
+                for (int o = 0; o < 7; ++o) e[o] = (int)r3[o - 3];
+                int* out = P + (size_t)(7 * m) * w + x;
+                out[0] = a0 + b[1] + c[2] + e[3];
+                out[w] = a0 + b[1] + c[3] + e[4];
+                out[2 * w] = a0 + b[2] + c[3] + e[5];
+                out[3 * w] = a0 + b[2] + c[4] + e[6];
+                out[4 * w] = a0 + b[1] + c[1] + e[2];
+                out[5 * w] = a0 + b[0] + c[1] + e[1];
+                out[6 * w] = a0 + b[0] + c[0] + e[0];
+            }
+        }
+        __syncthreads();
     }
-    a.xs[k] = x + r - (n - 1);
-    *a.score = (int)(kv >> 32) - 1;
+    unsigned long long best = 0;
+    for (int i = k - 1; i >= 0; --i) {
+        const bool top = i == k - 1;
+#pragma unroll
+        for (int q = 0; q < kRowsPer; ++q) {
+            const int r = ry + q * kRowLanes;
+            if (r >= D) break;
+            const int d = r - (n - 1);
+            const int s = d < 0 ? -d : d, sg = d < 0 ? -1 : 1;
+            // c[l] = ceil(s_l / 2), s_l = s >> (p - l): what level l adds to the
+            // offset of a row whose bit l-1 is set
+            int c[p + 1];
+#pragma unroll
+            for (int l = 1; l <= p; ++l) c[l] = ((s >> (p - l)) + 1) >> 1;
+            // where the parts of the line of (x, d) lie, from x
+            constexpr int PARTS = BLOCKS ? NB4 : N;
+            int off[PARTS];
+            if constexpr (BLOCKS) {
+                const int s2 = s >> (p - 2);
+                const int j = d >= 0 ? s2 : (s2 == 0 ? 0 : 3 + s2);
+#pragma unroll
+                for (int m = 0; m < PARTS; ++m) {
+                    int o = 0;
+#pragma unroll
+                    for (int l = 3; l <= p; ++l)
+                        if ((m >> (l - 3)) & 1) o += c[l];
+                    off[m] = ((i * NB4 + m) * 7 + j) * w + sg * o;
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < PARTS; ++m) {
+                    int o = 0;
+#pragma unroll
+                    for (int l = 1; l <= p; ++l)
+                        if ((m >> (l - 1)) & 1) o += c[l];
+                    off[m] = (i * n + m) * w + sg * o;
+                }
+            }
+            const int lo = wl[q], hi = wh[q];
+            for (int x = cx; x < w; x += 64) {
+                const int xp = x + d;
+                const bool valid = (unsigned)xp < (unsigned)w;
+                int val = -1;
+                if (valid) {
+                    int h = 0;
+#pragma unroll
+                    for (int m = 0; m < PARTS; ++m) {
+                        if constexpr (BLOCKS)
+                            h += P[off[m] + x];
+                        else
+                            h += (int)img[off[m] + x];
+                    }
+                    if (top) {
+                        val = h;  // V_{k-1}: the masked table
+                    } else {
+                        // ascending rows, four reads in flight; a later row wins only
+                        // when larger (-2: below every value, -1 marks a missing cell)
+                        int mx = -2, ia = lo;
+                        for (int r0 = lo; r0 <= hi; r0 += 4) {
+                            int v[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                v[u] = r0 + u <= hi ? Vp[(r0 + u) * w + xp] : -2;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const bool take = v[u] > mx;
+                                mx = take ? v[u] : mx;
+                                ia = take ? r0 + u : ia;
+                            }
+                        }
+                        val = mx >= 0 ? h + mx : -1;
+                        A[(size_t)i * cells + (size_t)r * w + xp] = (unsigned char)ia;
+                    }
+                    if (i == 0) {
+                        const unsigned long long kk = small_key(val, x, r, D);
+                        best = kk > best ? kk : best;
+                    }
+                }
+                if (i > 0) Vc[r * w + x] = val;
+            }
+        }
+        __syncthreads();
+        int* tmp = Vp;
+        Vp = Vc;
+        Vc = tmp;
+    }
+    small_finish<n, D>(a, best, part, A);
 }
 
 constexpr int kMaxDevices = 64;
 
 // The kernel's dynamic LDS limit, raised once per device (the attribute is
 // a property of the function on the current device).
-template <typename PixT, int N, int CAP>
-hipError_t allow_lds() {
-    static std::once_flag once[kMaxDevices];
-    static hipError_t rc[kMaxDevices];
+hipError_t allow_lds(const void* kernel, std::once_flag* once, hipError_t* rc, size_t most) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
         (void)hipGetLastError();
         return hipErrorInvalidDevice;
     }
     std::call_once(once[dev], [&] {
-        rc[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_small<PixT, N, CAP>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLds);
+        rc[dev] = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
     });
     return rc[dev];
 }
 
-template <typename PixT, int N, int CAP>
-hipError_t launch_small_n(const SmallPack<CAP>& pk, size_t lds, hipStream_t s) {
-    hipError_t e = allow_lds<PixT, N, CAP>();
+template <typename PixT, int N>
+hipError_t launch_small_n(const SmallPack<kSmallPack>& pk, size_t lds, hipStream_t s) {
+    static std::once_flag once[kMaxDevices];
+    static hipError_t rc[kMaxDevices];
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(&detect_small<PixT, N, kSmallPack>), once,
+                             rc, kSmallLds);
     if (e != hipSuccess) return e;
     TimedLaunch tl("detect_small", s);
-    hipLaunchKernelGGL((detect_small<PixT, N, CAP>), dim3(pk.count), dim3(kSmallThreads), lds, s,
-                       pk);
+    hipLaunchKernelGGL((detect_small<PixT, N, kSmallPack>), dim3(pk.count), dim3(kSmallThreads), lds,
+                       s, pk);
     return hipGetLastError();
 }
 
-template <typename PixT, int CAP>
-hipError_t launch_small_t(int n, const SmallPack<CAP>& pk, size_t lds, hipStream_t s) {
+template <typename PixT, int N>
+hipError_t launch_small_n(const SmallJob& job, size_t lds, hipStream_t s) {
+    static std::once_flag once[kMaxDevices];
+    static hipError_t rc[kMaxDevices];
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(&detect_small_one<PixT, N>), once, rc,
+                             kSmallOneLds);
+    if (e != hipSuccess) return e;
+    TimedLaunch tl("detect_small", s);
+    hipLaunchKernelGGL((detect_small_one<PixT, N>), dim3(1), dim3(kSmallThreads), lds, s, job);
+    return hipGetLastError();
+}
+
+// W: a pack of images or one image.
+template <typename PixT, typename W>
+hipError_t launch_small_t(int n, const W& work, size_t lds, hipStream_t s) {
     switch (n) {
-        case 1: return launch_small_n<PixT, 1, CAP>(pk, lds, s);
-        case 2: return launch_small_n<PixT, 2, CAP>(pk, lds, s);
-        case 4: return launch_small_n<PixT, 4, CAP>(pk, lds, s);
-        case 8: return launch_small_n<PixT, 8, CAP>(pk, lds, s);
-        case 16: return launch_small_n<PixT, 16, CAP>(pk, lds, s);
-        case 32: return launch_small_n<PixT, 32, CAP>(pk, lds, s);
+        case 1: return launch_small_n<PixT, 1>(work, lds, s);
+        case 2: return launch_small_n<PixT, 2>(work, lds, s);
+        case 4: return launch_small_n<PixT, 4>(work, lds, s);
+        case 8: return launch_small_n<PixT, 8>(work, lds, s);
+        case 16: return launch_small_n<PixT, 16>(work, lds, s);
+        case 32: return launch_small_n<PixT, 32>(work, lds, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -423,18 +630,19 @@ hipError_t launch_small_jobs(const SmallJobSpec* jobs, int count, hipStream_t s)
                 lds = std::max(lds, small_lds_bytes(J.g.n, J.g.w, J.g.k, dtype == 0 ? 1 : 2));
             };
             hipError_t e;
-            if (cnt == 1) {
-                SmallPack<1> pk{};
-                fill(pk.job[0], *group[q0]);
-                pk.count = 1;
-                e = dtype == 0 ? launch_small_t<uint8_t, 1>(n, pk, lds, s)
-                               : launch_small_t<uint16_t, 1>(n, pk, lds, s);
+            const Geometry& g0 = group[q0]->g;
+            const size_t lds_one = small_one_lds_bytes(g0.n, g0.w, g0.k, dtype == 0 ? 1 : 2);
+            if (cnt == 1 && lds_one <= kSmallOneLds) {
+                SmallJob job{};
+                fill(job, *group[q0]);
+                e = dtype == 0 ? launch_small_t<uint8_t>(n, job, lds_one, s)
+                               : launch_small_t<uint16_t>(n, job, lds_one, s);
             } else {
                 SmallPack<kSmallPack> pk{};
                 for (int q = 0; q < cnt; ++q) fill(pk.job[q], *group[q0 + q]);
                 pk.count = cnt;
-                e = dtype == 0 ? launch_small_t<uint8_t, kSmallPack>(n, pk, lds, s)
-                               : launch_small_t<uint16_t, kSmallPack>(n, pk, lds, s);
+                e = dtype == 0 ? launch_small_t<uint8_t>(n, pk, lds, s)
+                               : launch_small_t<uint16_t>(n, pk, lds, s);
             }
             if (e != hipSuccess) return e;
         }
