@@ -358,7 +358,7 @@ int fhtp_tune_get(fhtp_tune_rule* out, int cap, int* count);
  *   returns one entry per kernel family in order of first launch: the family
  *   name ("fht_reg_kernel" (the FHT's one-pass kernels), "fht_combine_kernel", "dp_pair_fixed",
  *   "dp_step_fixed", "dp_step_blocks", "argmax_table", "walk",
- *   "angle_windows", "prep_kernel", ...), its launch count and the summed
+ *   "prep_kernel", ...), its launch count and the summed
  *   elapsed time of its brackets in milliseconds.  Up to `cap` entries
  *   are written to `out` (host memory); *count receives the number of
  *   families.  FHTP_ERR_HIP if an event could not be read (the entries are

@@ -79,6 +79,8 @@ struct DpJob {
     unsigned long long* key;  // last step: one packed key per workgroup, else null
     int32_t* succ;            // last step: per key, the row of that cell's best successor
     const int32_t* win;       // mode-1 windows lo[D], hi[D], or null
+    int32_t* win_out;         // the image's first step makes them here, else null
+    double tan_gamma;
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w;
     int bound;    // mode-0 bound (block kernel)
@@ -1125,6 +1127,35 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     }
 }
 
+// Mode-1 window of displacement d: lo and hi bracket every d' with
+// n*|d'-d| <= t*(n*n + d*d').  Both sides are exact products of integers below
+// 2^22 except the one rounding of t times the integer, so the result does not
+// depend on how the compiler groups the arithmetic.  Each side of d is searched
+// by halving: rhs - lhs is linear in d' there and not negative at d' = d, so the
+// admissible d' are a run that ends at d (and where that run's end lies inside
+// the range, the slope is at least t*n/2, far above the rounding).
+__device__ __forceinline__ void angle_window(int n, double t, int d, int& lo, int& hi) {
+    auto admits = [&](int dp) {
+        return (double)(n * abs(dp - d)) <= t * (double)(n * n + d * dp);
+    };
+    int a = -(n - 1), b = d;  // the smallest admissible d' lies in [a, b]
+    while (a < b) {
+        const int m = a + ((b - a) >> 1);
+        const bool in = admits(m);
+        b = in ? m : b;
+        a = in ? a : m + 1;
+    }
+    lo = b;
+    a = d, b = n - 1;  // the largest
+    while (a < b) {
+        const int m = b - ((b - a) >> 1);
+        const bool in = admits(m);
+        a = in ? m : a;
+        b = in ? b : m - 1;
+    }
+    hi = a;
+}
+
 // Step with per-displacement windows [lo(d), hi(d)] (mode-0 bounds above the
 // fixed-window kernels', the angle form, and with a through-point pin no bound
 // at all): a workgroup owns COLS successor columns x' and every displacement
@@ -1255,7 +1286,17 @@ __global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(
     }
     for (int r = t; r < D; r += C::THREADS) {
         int lo, hi;
-        window_of(n, a.full, a.win, a.bound, r - (n - 1), lo, hi);
+        if (a.win_out) {
+            // the first step makes the angle form's windows for itself, and one
+            // of its workgroups leaves them to later launches
+            angle_window(n, a.tan_gamma, r - (n - 1), lo, hi);
+            if (local == 0) {
+                a.win_out[r] = lo;
+                a.win_out[D + r] = hi;
+            }
+        } else {
+            window_of(n, a.full, a.win, a.bound, r - (n - 1), lo, hi);
+        }
         wlo[r] = (unsigned short)(lo + n - 1);
         whi[r] = (unsigned short)(hi + n - 1);
     }
@@ -1744,33 +1785,14 @@ __global__ __launch_bounds__(64) void walk(WalkPack<CAP> pk) {
     }
 }
 
-// Mode-1 windows: lo(d) and hi(d) bracket every d' with n*|d'-d| <= t*(n*n + d*d').
-// One wave per d: the lanes test 64 candidates d' at a time and the first
-// and last admissible ones come from the wave's ballot.  Both sides of the
-// test are exact products of integers below 2^22 except the one rounding of
-// t times the integer, so the result does not depend on how the compiler
-// groups the arithmetic.
+// The windows of one image, for bands whose first step does not make them.
 __global__ __launch_bounds__(64) void angle_windows(int n, double t, int32_t* __restrict__ win) {
-    const int D = 2 * n - 1;
-    const int r = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int d = r - (n - 1);
-    int lo = n, hi = -n;
-    for (int q0 = 0; q0 < D; q0 += 64) {
-        const int q = q0 + lane;
-        const int dp = q - (n - 1);
-        const double lhs = (double)n * (double)abs(dp - d);
-        const double rhs = t * ((double)n * (double)n + (double)d * (double)dp);
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(q < D && lhs <= rhs);
-        if (m) {
-            if (lo == n) lo = q0 + (int)__builtin_ctzll(m) - (n - 1);
-            hi = q0 + 63 - (int)__builtin_clzll(m) - (n - 1);
-        }
-    }
-    if (lane == 0) {
-        win[r] = lo;
-        win[D + r] = hi;
-    }
+    const int D = 2 * n - 1, r = blockIdx.x * 64 + threadIdx.x;
+    if (r >= D) return;
+    int lo, hi;
+    angle_window(n, t, r - (n - 1), lo, hi);
+    win[r] = lo;
+    win[D + r] = hi;
 }
 
 // ---- unbounded bend: the column-maximum recurrence ---------------------------
@@ -2207,6 +2229,12 @@ void first_step_pin(const DpJobSpec& J, int& mode, int& x) {
     x = mode ? J.pin.x : 0;
 }
 
+// Whether the angle form's windows are made by the first step's workgroups (all of
+// them, each for itself) and not by a launch of their own: up to 511 displacements
+// (1024 x 1024, n = 64 81.6 against 82.7 us a detection, 511 displacements 93.4
+// against 94.2; 2047 displacements 196 against 192.5).
+bool first_step_windows(const Geometry& g) { return g.D <= 511; }
+
 // Common fields of an image's step descriptor.
 DpJob base_job(const DpJobSpec& J) {
     const Geometry& g = J.g;
@@ -2252,7 +2280,13 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
             a.aout = last ? nullptr : static_cast<AT*>(J->buf.a) + (size_t)(i - 1) * plane;
             a.key = last ? J->buf.key : nullptr;
             a.succ = last ? J->buf.succ : nullptr;
-            if (st == 0) first_step_pin(*J, a.vin_pin, a.vin_pin_x);
+            if (st == 0) {
+                first_step_pin(*J, a.vin_pin, a.vin_pin_x);
+                if (a.win && first_step_windows(g)) {
+                    a.win_out = J->buf.win;
+                    a.tan_gamma = J->plan.tan_gamma;
+                }
+            }
             a.out_pin_x = J->pin.j == i ? J->pin.x : -1;
             if (c.rows) {
                 cs.cols = blk_cols(g, CAP == 1, last);
@@ -2813,9 +2847,9 @@ hipError_t launch_dp_jobs(const DpJobSpec* jobs, int count, hipStream_t s) {
         if (J.plan.kind == WindowKind::Fixed &&
             (J.plan.bound < 0 || J.plan.bound > kMaxFixedB || (J.plan.dc != 8 && J.plan.dc != 16)))
             return hipErrorInvalidValue;
-        if (J.plan.kind == WindowKind::Angle) {
+        if (J.plan.kind == WindowKind::Angle && J.g.k >= 2 && !first_step_windows(J.g)) {
             TimedLaunch tl("angle_windows", s);
-            hipLaunchKernelGGL(angle_windows, dim3(J.g.D), dim3(64), 0, s, J.g.n,
+            hipLaunchKernelGGL(angle_windows, dim3((J.g.D + 63) / 64), dim3(64), 0, s, J.g.n,
                                J.plan.tan_gamma, J.buf.win);
         }
         (J.plan.a16 ? a16 : a8).push_back(&J);
