@@ -27,6 +27,7 @@
 // Global loads and table stores are coalesced along x.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 #include <vector>
 
 #include "fhtp_internal.h"
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
 // aligned addresses, put in place with the next lane's) took 65 us, eight waves
 // a workgroup 58.
 //
-// 8-bit pixels: a lane's register holds the right-leaning line's sum in its
+// 8-bit pixels (BOTH): a lane's register holds the right-leaning line's sum in its
 // low half and the left-leaning line's in its high half (both directions are
 // the same recursion in c-space, at the same c) while the sums cover at most
 // 128 rows (at most 128 * 255 < 2^16, no carry between the halves) and the last
@@ -462,14 +463,12 @@ struct SplitCfg {
     static constexpr int M = 8;                    // blocks
     static constexpr int NT = P <= 7 ? 1024 : 512;
     static constexpr int ROWS = NF * R;            // rows of a block
-    template <typename PixT>                       // pixels a lane holds of them
-    static constexpr int PX = ROWS * (sizeof(PixT) == 1 ? 2 : 1);
     static constexpr int WC = 57;                  // columns a wave of phase 1 makes
     static constexpr int CG = 5;                   // waves of phase 1 across
     // columns a workgroup produces, in two waves' halves: what CG WC leaves
     // after the skew f m and the residual shifts
     static constexpr int FIT = (CG * WC - (NF - 1) * (M - 1) - 7) / 4 * 4;
-    static constexpr int TC = FIT < 240 ? FIT : 240;  // at most 120 of a half wave's 128 are whole
+    static constexpr int TC = FIT < 240 ? FIT : 240;  // (120 of a half wave's 128 are whole)
     static constexpr int HC = TC / 2;
     static constexpr int PITCH = CG * WC + 8;      // (a half wave reads past its columns)
     // levels of phase 2 that 8-bit pixels run unpacked: the last one, and
@@ -534,15 +533,14 @@ struct SplitItem {
 
 // The pixels of one wave of phase 1: the rows of block m at c-space column cb +
 // lane, base sum q read g (NF m + q) columns to its right (cb uniform); p[i]
-// of row i, 8-bit pixels the right-leaning column's in p[i] and the
-// left-leaning one's in p[ROWS + i].
-template <int P, typename PixT>
+// of row i; with BOTH the right-leaning column's in p[i] and the left-leaning
+// one's in p[ROWS + i].
+template <int P, bool BOTH, typename PixT>
 __device__ __forceinline__ void split_load(const FhtJob& J, const SplitItem& it, int m, int cb,
-                                           uint32_t (&p)[SplitCfg<P>::template PX<PixT>]) {
+                                           uint32_t (&p)[SplitCfg<P>::ROWS * (BOTH ? 2 : 1)]) {
     using C = SplitCfg<P>;
     constexpr int ROWS = C::ROWS;
     constexpr int sz = (int)sizeof(PixT);
-    constexpr bool BOTH = sz == 1;
     const int lane = threadIdx.x & 63;
     const int w = J.w, W = J.W, g = it.g, dir = it.dir;
     const int step = w * sz;
@@ -600,14 +598,14 @@ __device__ __forceinline__ void split_load(const FhtJob& J, const SplitItem& it,
 }
 
 // The fine sums v[f] of those pixels.
-template <int P, typename PixT>
-__device__ __forceinline__ void split_fine(const uint32_t (&p)[SplitCfg<P>::template PX<PixT>],
+template <int P, bool BOTH, typename PixT>
+__device__ __forceinline__ void split_fine(const uint32_t (&p)[SplitCfg<P>::ROWS * (BOTH ? 2 : 1)],
                                            int32_t (&v)[SplitCfg<P>::NF][1]) {
     using C = SplitCfg<P>;
 #pragma unroll
     for (int i = 0; i < C::ROWS; ++i) {
         uint32_t t = p[i];
-        if constexpr (sizeof(PixT) == 1) t |= p[C::ROWS + i] << 16;
+        if constexpr (BOTH) t |= p[C::ROWS + i] << 16;
         v[i / C::R][0] = i % C::R == 0 ? (int32_t)t : v[i / C::R][0] + (int32_t)t;
     }
     lane_stages<C::NF, 1, 1, C::LF>(v);
@@ -623,38 +621,52 @@ __device__ __forceinline__ void split_rows(char* base, int W, int x, bool two, b
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, 8u * row);
     unsigned int so = REV ? 7u * row : 0u;
     const int xa = (REV && two ? x - 1 : x) * esz;
-    // the parity of a row's pairs is the same on every lane (c is even)
-    const int odd = __builtin_amdgcn_readfirstlane(
-        (int)(((uint32_t)reinterpret_cast<uintptr_t>(base) + (uint32_t)xa) >> 1));
+    // Rows with the pair stores of even e and of odd e aligned or not (16-bit
+    // elements: one aligned 32-bit store, or two of 16 bits).
+    auto rows = [&](auto even_ok, auto odd_ok) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (e > 0 || !skip0) {
-            const uint32_t a = (uint32_t)v[e][REV ? 1 : 0], b = (uint32_t)v[e][REV ? 0 : 1];
-            if (two) {
-                if constexpr (E16) {
-                    // one aligned 32-bit store, or two of 16 bits
-                    if (((odd + (REV ? 7 - e : e) * W) & 1) == 0) {
-                        __builtin_amdgcn_raw_buffer_store_b32(a | (b << 16), rs, xa, (int)so, 0);
-                    } else {
-                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)a, rs, xa, (int)so, 0);
-                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, rs, xa + 2, (int)so, 0);
-                    }
-                } else {
+        for (int e = 0; e < 8; ++e) {
+            if (e > 0 || !skip0) {
+                const uint32_t a = (uint32_t)v[e][REV ? 1 : 0], b = (uint32_t)v[e][REV ? 0 : 1];
+                const bool ok = (e & 1) ? decltype(odd_ok)::value : decltype(even_ok)::value;
+                if (!two) {
+                    const uint32_t o = (uint32_t)v[e][0];
+                    if constexpr (E16)
+                        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)o, rs, xa, (int)so, 0);
+                    else
+                        __builtin_amdgcn_raw_buffer_store_b32(o, rs, xa, (int)so, 0);
+                } else if constexpr (!E16) {
                     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                     u32x2 t;
                     t.x = a;
                     t.y = b;
                     __builtin_amdgcn_raw_buffer_store_b64(t, rs, xa, (int)so, 0);
+                } else if (ok) {
+                    __builtin_amdgcn_raw_buffer_store_b32(a | (b << 16), rs, xa, (int)so, 0);
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)a, rs, xa, (int)so, 0);
+                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)b, rs, xa + 2, (int)so, 0);
                 }
-            } else {
-                const uint32_t o = (uint32_t)v[e][0];
-                if constexpr (E16)
-                    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)o, rs, xa, (int)so, 0);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b32(o, rs, xa, (int)so, 0);
             }
+            so = REV ? so - row : so + row;
         }
-        so = REV ? so - row : so + row;
+    };
+    if (E16 && two) {
+        // the parity of a row's pairs is the same on every lane (c is even)
+        const int first = __builtin_amdgcn_readfirstlane(
+            (int)(((uint32_t)reinterpret_cast<uintptr_t>(base) + (uint32_t)xa) >> 1));
+        const bool ok0 = ((first + (REV ? 7 : 0) * W) & 1) == 0;
+        const bool ok1 = ((first + (REV ? 6 : 1) * W) & 1) == 0;
+        if (ok0 && ok1)
+            rows(std::true_type{}, std::true_type{});
+        else if (ok0)
+            rows(std::true_type{}, std::false_type{});
+        else if (ok1)
+            rows(std::false_type{}, std::true_type{});
+        else
+            rows(std::false_type{}, std::false_type{});
+    } else {
+        rows(std::true_type{}, std::true_type{});
     }
 }
 
@@ -671,8 +683,7 @@ __device__ __forceinline__ void split_cols(char* base, int W, int ct, int c, int
 template <int P, typename PixT>
 __device__ __forceinline__ void split_store(const FhtJob& J, int blk, int dir, int s0, int ct, int c,
                                             int lim, const int32_t (&v)[8][2]) {
-    using C = SplitCfg<P>;
-    constexpr int N = C::N, D = 2 * N - 1;
+    constexpr int N = 1 << P, D = 2 * N - 1;
     const int W = J.W;
     // The 8 rows' first one in memory: rows N-1 + s or, leaning left, N-1 - s
     // of the table; row s of the scratch.
@@ -735,10 +746,9 @@ __device__ __forceinline__ SplitItem split_item(const FhtPack<CAP>& pk, int b) {
     return it;
 }
 
-template <int P, typename PixT, int CAP>
+template <int P, bool BOTH, typename PixT, int CAP>
 __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_split_kernel(FhtPack<CAP> pk) {
     using C = SplitCfg<P>;
-    constexpr bool BOTH = sizeof(PixT) == 1;
     constexpr int WAVES = C::NT / 64;
     __shared__ int32_t fine[C::M * C::NF * C::PITCH];  // [m][f][column]
     const int lane = threadIdx.x & 63;
@@ -751,10 +761,10 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
 #pragma unroll 1
     for (int task = wave; task < C::M * C::CG; task += WAVES) {
         const int m = task % C::M, cg = task / C::M;
-        uint32_t px[C::template PX<PixT>];
-        split_load<P, PixT>(J, it, m, it.ct + cg * C::WC, px);
+        uint32_t px[C::ROWS * (BOTH ? 2 : 1)];
+        split_load<P, BOTH, PixT>(J, it, m, it.ct + cg * C::WC, px);
         int32_t v[C::NF][1];
-        split_fine<P, PixT>(px, v);
+        split_fine<P, BOTH, PixT>(px, v);
         if (lane < C::WC) {
 #pragma unroll
             for (int f = 0; f < C::NF; ++f)
@@ -987,8 +997,8 @@ hipError_t launch_reg_pack(const RegRun* runs, int count, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int P, typename PixT, int CAP>
-hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) {
+template <int P, bool BOTH, typename PixT, int CAP>
+hipError_t launch_split_as(const RegRun* runs, int count, hipStream_t stream) {
     using C = SplitCfg<P>;
     FhtPack<CAP> pk{};
     long long total = 0;
@@ -1008,7 +1018,7 @@ hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) 
         J.out16 = r.out16;
         J.narrow = r.narrow;
         J.sub16 = r.sub16;
-        total += (long long)tiles * r.blocks * C::G * (sizeof(PixT) == 1 ? 1 : 2);
+        total += (long long)tiles * r.blocks * C::G * (BOTH ? 1 : 2);
         if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     }
     pk.count = count;
@@ -1019,10 +1029,29 @@ hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) 
     // the one before: 57.5 against 53.9 us at 4096 x 4096, n = 128, 16 bits).
     {
         TimedLaunch tl("fht_reg_kernel", stream);  // one family: the band transform
-        hipLaunchKernelGGL((fht_split_kernel<P, PixT, CAP>), dim3((unsigned)total), dim3(C::NT), 0,
+        hipLaunchKernelGGL((fht_split_kernel<P, BOTH, PixT, CAP>), dim3((unsigned)total), dim3(C::NT), 0,
                            stream, pk);
     }
     return hipGetLastError();
+}
+
+// 8-bit pixels: both directions in a workgroup, but one where that would leave
+// the chip's workgroup slots (two a CU) idle.  Both / one, us in a detection: 80
+// items (1024 x 1024, n = 64) 10.1 / 8.5, 96 (n = 128) 11.9 / 9.3, 320 (2048 x
+// 2048, n = 128) 18.3 / 16.2, 352 (2048 x 2047, n = 256) 35.1 / 32.5, but 448
+// (2048 x 3000, n = 64) 14.1 / 15.3 and 1184 (4096 x 4096, n = 128) 37.4 / 40.3.
+constexpr long long kOneWayItems = 384;
+
+template <int P, typename PixT, int CAP>
+hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) {
+    using C = SplitCfg<P>;
+    if constexpr (sizeof(PixT) == 1) {
+        long long items = 0;
+        for (int q = 0; q < count; ++q)
+            items += (long long)((runs[q].W + C::TC - 1) / C::TC) * runs[q].blocks * C::G;
+        if (items > kOneWayItems) return launch_split_as<P, true, PixT, CAP>(runs, count, stream);
+    }
+    return launch_split_as<P, false, PixT, CAP>(runs, count, stream);
 }
 
 // Largest band height (as a power of two) made in one pass, and the smallest
