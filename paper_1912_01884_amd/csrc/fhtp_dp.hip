@@ -69,6 +69,13 @@ constexpr int kXcds = 8;       // accelerator dies of the MI355X, each with its 
 // of in the L2 write-back at its end, which sits on the critical path of the
 // chain of step launches (about 1.2 us per launch at 4096 x 255 cells).
 constexpr int kStoreScope = 16;
+// Pair launches that move more than this leave V_i to the L2s (32 MB in all, which
+// such a launch turns over anyway; then a written-through plane only waits for
+// memory).  Written through / not, us a detection: 28 MB a launch (2048 x 6000,
+// 16-bit, k = 16) 109.2 / 109.6, 29 (2048 x 8192, 8-bit) 105.8 / 108.4, 32 (4096 x
+// 3000, k = 16) 140.5 / 136.3, 38 (2048 x 8192, 16-bit) 141.6 / 137.2, 75 (16384 x
+// 16384, k = 128) 2196 / 2106; 256 mixed images 1553 / 1507.
+constexpr size_t kThroughBytes = 30000000;
 
 // One image in one step launch.
 struct DpJob {
@@ -656,6 +663,23 @@ constexpr int kPairDC = 8;                       // phase 2: displacements per t
 constexpr int kPairRows = kPairWaves * kPairDC;  // displacements of step i per workgroup
 constexpr int kStrip = 16;                       // phase 1: displacements per thread
 
+// Shape of a pair launch's workgroups.  On a grid of at most kSmallGrid of the
+// usual ones (one a CU) a launch is as long as one workgroup's chain of loads and
+// window maxima, so each is made shorter: 8 waves of 2 displacements, strips of 8,
+// twice the workgroups with half the cells, each of their threads about a third of
+// the work, for more halo.  Usual / small, us a detection: 20 workgroups (1024 x
+// 600, n = 32, bound 4) 82.5 / 68.0, 64 (1024 x 1024, n = 64) 47.2 / 40.4, 128 (1024
+// x 2000, n = 64, bound 8) 51.7 / 47.9, 256 (2048 x 2048, n = 128, bound 6) 58.8 /
+// 58.1, but 512 (4096 x 4096, n = 128, bound 8) 165 / 186.
+constexpr int kSmallGrid = 256;
+template <bool SMALL>
+struct PairShape {
+    static constexpr int WAVES = SMALL ? 8 : kPairWaves;
+    static constexpr int DC = SMALL ? 2 : kPairDC;
+    static constexpr int ROWS = WAVES * DC;
+    static constexpr int STRIP = SMALL ? 8 : kStrip;
+};
+
 struct DpPairJob {
     const int32_t* vin;  // V_{i+2} (or the table H_{k-1}), rows d''+n-1
     const void* h1;      // H_{i+1} (int32, or uint16 for narrow tables: the kernel's TT)
@@ -680,7 +704,8 @@ template <int CAP>
 struct DpPairPack {
     DpPairJob job[CAP];
     int count;
-    int stripe;  // column tiles per stripe of the item order (tuned; 16 by default)
+    int stripe;   // column tiles per stripe of the item order
+    int through;  // write V_i through to memory (see kThroughBytes)
 };
 
 // Masks: a thread's loads of V_{i+2} are consecutive rows of one column, so
@@ -692,17 +717,20 @@ struct DpPairPack {
 // the view's extent.
 // PIN: the through-point masks (a separate instantiation, so that unpinned
 // launches carry none of their instructions or registers).
-template <int B, typename AT, int CAP, bool PIN, typename TT>
-__global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP> pk) {
-    constexpr int RM = kPairRows + 2 * B;  // rows of V_{i+1} the workgroup needs
-    constexpr int NS = (RM + kStrip - 1) / kStrip;
-    constexpr int SC = 64 + kStrip - 1;    // successor columns of one strip
-    constexpr int NV1 = kStrip + 2 * B;
-    constexpr int NV2 = kPairDC + 2 * B;
-    constexpr int LP = kStrip - 1;         // padding on either side of an LDS row
+// SMALL: the shape for small grids (PairShape).
+template <int B, typename AT, int CAP, bool PIN, typename TT, bool SMALL>
+__global__ __launch_bounds__((64 * PairShape<SMALL>::WAVES)) void dp_pair_fixed(DpPairPack<CAP> pk) {
+    constexpr int WAVES = PairShape<SMALL>::WAVES, DC = PairShape<SMALL>::DC;
+    constexpr int STRIP = PairShape<SMALL>::STRIP, ROWS = PairShape<SMALL>::ROWS;
+    constexpr int RM = ROWS + 2 * B;  // rows of V_{i+1} the workgroup needs
+    constexpr int NS = (RM + STRIP - 1) / STRIP;
+    constexpr int SC = 64 + STRIP - 1;    // successor columns of one strip
+    constexpr int NV1 = STRIP + 2 * B;
+    constexpr int NV2 = DC + 2 * B;
+    constexpr int LP = STRIP - 1;         // padding on either side of an LDS row
     constexpr int LWP = 64 + 2 * LP;       // strip cells outside the tile land in the padding
-    __shared__ int mid[NS * kStrip][LWP];  // V_{i+1}(X0 + c, row m0 + q) at [q][LP + c]
-    __shared__ AT nxt[NS * kStrip][LWP];   // row of that cell's window maximum (its choice)
+    __shared__ int mid[NS * STRIP][LWP];  // V_{i+1}(X0 + c, row m0 + q) at [q][LP + c]
+    __shared__ AT nxt[NS * STRIP][LWP];   // row of that cell's window maximum (its choice)
 
     // Workgroup b runs on XCD b % 8.  Each XCD gets a contiguous run of items
     // instead, an image's items in stripes of pk.stripe column tiles (every
@@ -735,7 +763,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP>
         bx = st * stripe + (loc - by * sw);
     }
     const int X0 = bx * 64;
-    const int r0 = by * kPairRows;  // table row of the first displacement of step i
+    const int r0 = by * ROWS;  // table row of the first displacement of step i
     const int m0 = r0 - B;          // table row of mid[0]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -745,22 +773,22 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP>
     // Phase 2's H_i(x' - d, d), issued first so that the loads overlap phase 1.
     const int xp = X0 + lane;
     const bool col_ok = xp < w;
-    const int r2 = r0 + wave * kPairDC;
+    const int r2 = r0 + wave * DC;
     const int d2 = r2 - (n - 1);
-    const RowView h0v = row_view(a.h0, a.h_pitch, (int)hsz, r2, kPairDC, D);
+    const RowView h0v = row_view(a.h0, a.h_pitch, (int)hsz, r2, DC, D);
     const unsigned int h0b = (unsigned int)(r2 - h0v.base) * hp + (unsigned int)(xp - d2) * hsz;
-    int hv0[kPairDC];
+    int hv0[DC];
 #pragma unroll
-    for (int j = 0; j < kPairDC; ++j) hv0[j] = load_tab<TT>(h0v.rs, h0b + j * (hp - hsz), 0);
+    for (int j = 0; j < DC; ++j) hv0[j] = load_tab<TT>(h0v.rs, h0b + j * (hp - hsz), 0);
 
-    // Phase 1.  Views: V_{i+2} rows [m0 - B, m0 + NS*kStrip + B), H_{i+1} rows
+    // Phase 1.  Views: V_{i+2} rows [m0 - B, m0 + NS*STRIP + B), H_{i+1} rows
     // [m0, m0 + RM), each clipped to [0, D).
-    const RowView vv = row_view(a.vin, a.vin_pitch, 4, m0 - B, NS * kStrip + 2 * B, D);
+    const RowView vv = row_view(a.vin, a.vin_pitch, 4, m0 - B, NS * STRIP + 2 * B, D);
     const RowView h1v = row_view(a.h1, a.h_pitch, (int)hsz, m0, RM, D);
     const unsigned int vp = (unsigned int)a.vin_pitch * 4u;
-    for (int t = threadIdx.x; t < NS * SC; t += 64 * kPairWaves) {
+    for (int t = threadIdx.x; t < NS * SC; t += 64 * WAVES) {
         const int s = t / SC, c = t - s * SC;
-        const int q0 = s * kStrip;             // mid row of the strip's first displacement
+        const int q0 = s * STRIP;             // mid row of the strip's first displacement
         const int rs = m0 + q0;                // its table row
         const int xs = X0 + rs - (n - 1) + c;  // successor column x''
         const bool xs_ok = (unsigned)xs < (unsigned)w;
@@ -782,7 +810,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP>
         int* lrow = &mid[q0][LP + c];
         AT* nrow = &nxt[q0][LP + c];
         // A wave whose every load and cell is valid takes the unmasked copy.
-        const bool inner = qlo <= 0 && qhi >= NV1 && jlo <= 0 && jhi >= kStrip && (!PIN || a.pin1_x < 0);
+        const bool inner = qlo <= 0 && qhi >= NV1 && jlo <= 0 && jhi >= STRIP && (!PIN || a.pin1_x < 0);
         auto strip = [&](auto inner_tag) {
             constexpr bool INNER = decltype(inner_tag)::value;
             int v[NV1];
@@ -798,15 +826,15 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP>
                 }
             }
             // H_{i+1}(x', d') at x' = X0 + c - j, row rs + j
-            int hv[kStrip];
+            int hv[STRIP];
 #pragma unroll
-            for (int j = 0; j < kStrip; ++j)
+            for (int j = 0; j < STRIP; ++j)
                 hv[j] = load_tab<TT>(h1v.rs, hb + j * (hp - hsz), 0);
             __builtin_amdgcn_sched_barrier(0);
-            int m[kStrip], ia[kStrip];
-            window_max<B, kStrip>(v, m, ia);
+            int m[STRIP], ia[STRIP];
+            window_max<B, STRIP>(v, m, ia);
 #pragma unroll
-            for (int j = 0; j < kStrip; ++j) {
+            for (int j = 0; j < STRIP; ++j) {
                 const bool live =
                     INNER || (j >= jlo && j < jhi && (!PIN || a.pin1_x < 0 || X0 + c - j == a.pin1_x));
                 const int val = live && m[j] >= 0 ? hv[j] + m[j] : -1;
@@ -825,39 +853,45 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_pair_fixed(DpPairPack<CAP>
     // Phase 2: step i on the LDS copy of V_{i+1}; rows outside [0, D) and
     // cells without a successor column hold -1.
     int v2[NV2];
-    const int* lcol = &mid[wave * kPairDC][LP + lane];
+    const int* lcol = &mid[wave * DC][LP + lane];
 #pragma unroll
     for (int q = 0; q < NV2; ++q) v2[q] = lcol[q * LWP];
-    int m2[kPairDC], ia2[kPairDC];
-    window_max<B, kPairDC>(v2, m2, ia2);
+    int m2[DC], ia2[DC];
+    window_max<B, DC>(v2, m2, ia2);
     constexpr int psz = (int)sizeof(PairLinks<AT>);
-    const RowView aview = row_view(a.a, a.a_pitch, psz, r2, kPairDC, D);
-    const RowView oview = row_view(a.vout, a.v_pitch, 4, r2, kPairDC, D);
+    const RowView aview = row_view(a.a, a.a_pitch, psz, r2, DC, D);
+    const RowView oview = row_view(a.vout, a.v_pitch, 4, r2, DC, D);
     const unsigned int op = (unsigned int)a.v_pitch * 4u;
     // cell j: row r2 + j < D; V_i(x, d) at x = xp - d2 - j in [0, w)
-    const int jn = col_ok ? min(kPairDC, D - r2) : 0;
+    const int jn = col_ok ? min(DC, D - r2) : 0;
     const int xj = xp - d2;  // x of cell j is xj - j
     const unsigned int ob = (unsigned int)xj * 4u;
     const unsigned int ab2 = (unsigned int)xp * (unsigned int)psz;
     const unsigned int pp = (unsigned int)a.a_pitch * (unsigned int)psz;
+    auto cells = [&](auto scope) {
 #pragma unroll
-    for (int j = 0; j < kPairDC; ++j) {
-        const bool cell = j < jn;
-        const bool live = cell && (unsigned)(xj - j) < (unsigned)w;
-        const int val =
-            m2[j] >= 0 && (!PIN || a.pin0_x < 0 || xj - j == a.pin0_x) ? hv0[j] + m2[j] : -1;
-        const int ra = r2 - B + ia2[j];
-        const unsigned int av = (unsigned int)(ra < 0 ? 0 : ra);
-        const unsigned int av2 = nxt[wave * kPairDC + ia2[j]][LP + lane];  // the chosen cell's choice
-        const unsigned int aoff = cell ? ab2 + j * pp : kOut;
-        const unsigned int both = av | (av2 << kLinkBits<AT>);
-        if constexpr (sizeof(AT) == 1)
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)both, aview.rs, (int)aoff, 0, kStoreScope);
-        else
-            __builtin_amdgcn_raw_buffer_store_b32(both, aview.rs, (int)aoff, 0, kStoreScope);
-        __builtin_amdgcn_raw_buffer_store_b32(val, oview.rs, (int)(live ? ob + j * (op - 4u) : kOut),
-                                              0, kStoreScope);
-    }
+        for (int j = 0; j < DC; ++j) {
+            const bool cell = j < jn;
+            const bool live = cell && (unsigned)(xj - j) < (unsigned)w;
+            const int val =
+                m2[j] >= 0 && (!PIN || a.pin0_x < 0 || xj - j == a.pin0_x) ? hv0[j] + m2[j] : -1;
+            const int ra = r2 - B + ia2[j];
+            const unsigned int av = (unsigned int)(ra < 0 ? 0 : ra);
+            const unsigned int av2 = nxt[wave * DC + ia2[j]][LP + lane];  // the chosen cell's choice
+            const unsigned int aoff = cell ? ab2 + j * pp : kOut;
+            const unsigned int both = av | (av2 << kLinkBits<AT>);
+            if constexpr (sizeof(AT) == 1)
+                __builtin_amdgcn_raw_buffer_store_b16((unsigned short)both, aview.rs, (int)aoff, 0, kStoreScope);
+            else
+                __builtin_amdgcn_raw_buffer_store_b32(both, aview.rs, (int)aoff, 0, kStoreScope);
+            __builtin_amdgcn_raw_buffer_store_b32(val, oview.rs, (int)(live ? ob + j * (op - 4u) : kOut),
+                                                  0, decltype(scope)::value);
+        }
+    };
+    if (SMALL || pk.through)
+        cells(std::integral_constant<int, kStoreScope>{});
+    else
+        cells(std::integral_constant<int, 0>{});
 }
 
 // Three steps per launch (fixed windows of at most kTriMaxB shifts): the
@@ -2309,12 +2343,12 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
     return hipSuccess;
 }
 
-template <typename AT, int CAP, bool PIN, typename TT>
+template <typename AT, int CAP, bool PIN, typename TT, bool SMALL>
 hipError_t launch_pair_p(int bound, hipStream_t s, int grid, const DpPairPack<CAP>& pk) {
 #define FHTP_B(BB)                                                                         \
     case BB:                                                                               \
-        hipLaunchKernelGGL((dp_pair_fixed<BB, AT, CAP, PIN, TT>), dim3(grid),              \
-                           dim3(64 * kPairWaves), 0, s, pk);                               \
+        hipLaunchKernelGGL((dp_pair_fixed<BB, AT, CAP, PIN, TT, SMALL>), dim3(grid),       \
+                           dim3(64 * PairShape<SMALL>::WAVES), 0, s, pk);                  \
         return hipSuccess;
     switch (bound) {
         FHTP_B(0) FHTP_B(1) FHTP_B(2) FHTP_B(3) FHTP_B(4) FHTP_B(5) FHTP_B(6) FHTP_B(7) FHTP_B(8)
@@ -2324,23 +2358,24 @@ hipError_t launch_pair_p(int bound, hipStream_t s, int grid, const DpPairPack<CA
 #undef FHTP_B
 }
 
-// Pinned packs exist only for single images (a batch job has no pin).
+// Pins and the small shape are for a launch of one image.
 template <typename AT, int CAP, typename TT>
-hipError_t launch_pair_t(int bound, bool pinned, hipStream_t s, int grid,
+hipError_t launch_pair_t(int bound, bool pinned, bool small, hipStream_t s, int grid,
                          const DpPairPack<CAP>& pk) {
     if constexpr (CAP == 1) {
-        if (pinned) return launch_pair_p<AT, CAP, true, TT>(bound, s, grid, pk);
-    } else {
-        if (pinned) return hipErrorInvalidValue;
+        if (small)
+            return pinned ? launch_pair_p<AT, CAP, true, TT, true>(bound, s, grid, pk)
+                          : launch_pair_p<AT, CAP, false, TT, true>(bound, s, grid, pk);
+        if (pinned) return launch_pair_p<AT, CAP, true, TT, false>(bound, s, grid, pk);
     }
-    return launch_pair_p<AT, CAP, false, TT>(bound, s, grid, pk);
+    return launch_pair_p<AT, CAP, false, TT, false>(bound, s, grid, pk);
 }
 
 template <typename AT, int CAP>
-hipError_t launch_pair(int bound, bool pinned, bool narrow, hipStream_t s, int grid,
+hipError_t launch_pair(int bound, bool pinned, bool small, bool narrow, hipStream_t s, int grid,
                        const DpPairPack<CAP>& pk) {
-    return narrow ? launch_pair_t<AT, CAP, uint16_t>(bound, pinned, s, grid, pk)
-                  : launch_pair_t<AT, CAP, int32_t>(bound, pinned, s, grid, pk);
+    return narrow ? launch_pair_t<AT, CAP, uint16_t>(bound, pinned, small, s, grid, pk)
+                  : launch_pair_t<AT, CAP, int32_t>(bound, pinned, small, s, grid, pk);
 }
 
 template <typename AT, int CAP, typename TT>
@@ -2448,6 +2483,11 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
         hipError_t e = launch_step<AT, CAP>(c, s, pk);
         if (e != hipSuccess) return e;
     }
+    // The shape of the pair launches' workgroups.
+    const Geometry& g0 = jobs[0]->g;
+    const bool small = CAP == 1 && (long long)((g0.w + 63) / 64) *
+                                           ((g0.D + kPairRows - 1) / kPairRows) <= kSmallGrid;
+    const int pair_rows = small ? PairShape<true>::ROWS : PairShape<false>::ROWS;
     // A pair launch: image J's pair with phase-1 band i, as its V-launch j.
     auto pair_job = [&](const DpJobSpec& J, int i, int j, DpPairJob& a) {
         const Geometry& g = J.g;
@@ -2468,15 +2508,22 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
         a.n = g.n;
         a.w = g.w;
         a.items_x = (g.w + 63) / 64;
-        a.items_y = (g.D + kPairRows - 1) / kPairRows;
+        a.items_y = (g.D + pair_rows - 1) / pair_rows;
     };
     auto launch_pairs = [&](DpPairPack<CAP>& pk, int cnt, long long total) {
         pk.count = cnt;
         pk.stripe = std::max(1, c.stripe);
         bool pinned = false;
-        for (int q = 0; q < cnt; ++q)
-            pinned = pinned || pk.job[q].vin_pin != 0 || pk.job[q].pin1_x >= 0 || pk.job[q].pin0_x >= 0;
-        return launch_pair<AT, CAP>(jobs[0]->plan.bound, pinned, c.narrow, s, (int)total, pk);
+        size_t bytes = 0;  // two tables and V_{i+2} read, V_i and the links written
+        for (int q = 0; q < cnt; ++q) {
+            const DpPairJob& a = pk.job[q];
+            pinned = pinned || a.vin_pin != 0 || a.pin1_x >= 0 || a.pin0_x >= 0;
+            bytes += (size_t)(2 * a.n - 1) *
+                     ((size_t)a.h_pitch * 2 * (c.narrow ? 2 : 4) +
+                      (size_t)a.v_pitch * (2 * sizeof(int32_t) + sizeof(PairLinks<AT>)));
+        }
+        pk.through = bytes <= kThroughBytes;
+        return launch_pair<AT, CAP>(jobs[0]->plan.bound, pinned, small, c.narrow, s, (int)total, pk);
     };
     if (head_pairs) {  // G = 3: two top bands left over
         DpPairPack<CAP> pk{};
