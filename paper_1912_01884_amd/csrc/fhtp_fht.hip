@@ -19,8 +19,7 @@
 //     running sums of that column in VGPRs through all p stages; the operand
 //     that comes from another column (c + ceil(s/2)) is exchanged through LDS
 //     once per stage;
-//   - taller ones, up to 128 rows of 8-bit pixels and 512 of 16-bit ones,
-//     fht_split_kernel: the fine and the coarse levels of a group of shifts
+//   - taller ones, up to 256 rows, fht_split_kernel: the fine and the coarse levels of a group of shifts
 //     run on lanes, and a sum goes through LDS once, in between;
 //   - the rest: fht_split_kernel on 128-row sub-blocks, then
 //     fht_combine_kernel adds the sub-blocks along the coarse levels.
@@ -408,7 +407,7 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
     }
 }
 
-// ---- bands of 2^5 .. 2^9 rows ---------------------------------------------------
+// ---- bands of 2^5 .. 2^8 rows ---------------------------------------------------
 //
 // The shifts s of a band are taken in groups that share their top Q bits g.
 // Inside a group the recursion splits into three parts:
@@ -449,9 +448,9 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
 //
 // 8-bit pixels (BOTH): a lane's register holds the right-leaning line's sum in its
 // low half and the left-leaning line's in its high half (both directions are
-// the same recursion in c-space, at the same c) while the sums cover at most
-// 128 rows (at most 128 * 255 < 2^16, no carry between the halves) and the last
-// level of the band is still to come; the last levels run on 32 bits apart.
+// the same recursion in c-space, at the same c) up to the last level (sums of at
+// most 64 rows, 64 * 255 < 2^16: no carry between the halves), which runs on 32
+// bits apart.  Bands of at most 128 rows.
 template <int P>
 struct SplitCfg {
     static constexpr int N = 1 << P;
@@ -471,9 +470,6 @@ struct SplitCfg {
     static constexpr int TC = FIT < 240 ? FIT : 240;  // (120 of a half wave's 128 are whole)
     static constexpr int HC = TC / 2;
     static constexpr int PITCH = CG * WC + 8;      // (a half wave reads past its columns)
-    // levels of phase 2 that 8-bit pixels run unpacked: the last one, and
-    // those whose sums cover more than 128 rows
-    static constexpr int UNPACKED = P <= 8 ? 1 : P - 7;
 };
 
 // One level of the recursion on the COLS (1 or 2) adjacent columns of a lane,
@@ -788,7 +784,7 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
         const int s0 = (it.g * C::NF + f) * 8;
         const bool st = 2 * lane < C::HC;
         if constexpr (BOTH) {
-            lane_stages<8, 2, 1, 3 - C::UNPACKED>(v);
+            lane_stages<8, 2, 1, 2>(v);
             int32_t r[8][2];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -797,9 +793,9 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
                 v[e][0] = (int32_t)((uint32_t)v[e][0] >> 16);
                 v[e][1] = (int32_t)((uint32_t)v[e][1] >> 16);
             }
-            lane_stages<8, 2, 4 - C::UNPACKED, 3>(r);
+            lane_stages<8, 2, 3, 3>(r);
             if (st) split_store<P, PixT>(J, it.blk, 0, s0, it.ct, c, lim, r);
-            lane_stages<8, 2, 4 - C::UNPACKED, 3>(v);
+            lane_stages<8, 2, 3, 3>(v);
             if (st) split_store<P, PixT>(J, it.blk, 1, s0, it.ct, c, lim, v);
         } else {
             lane_stages<8, 2, 1, 3>(v);
@@ -808,7 +804,7 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
     }
 }
 
-// Pass 2 for bands of n = 2^p > 2^7 rows: the band is M = n/128 sub-blocks whose
+// Pass 2 for bands of n = 2^p > 2^8 rows: the band is M = n/128 sub-blocks whose
 // FHTs (fine shift sf = s >> (p-7)) sit in `sub`; the line of shift s starts in
 // sub-block m at c + D_s(m*128), so T(c, s) = sum_m sub[m][sf][(c + D_s(128 m)) mod W].
 // A workgroup covers 256 columns of one (band, direction) for kShiftGroup
@@ -1035,8 +1031,9 @@ hipError_t launch_split_as(const RegRun* runs, int count, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// 8-bit pixels: both directions in a workgroup, but one where that would leave
-// the chip's workgroup slots (two a CU) idle.  Both / one, us in a detection: 80
+// 8-bit pixels: both directions in a workgroup, but one for 256-row bands (4096 x
+// 4096 85.3 / 68.8 us) and where both would leave the chip's workgroup slots (two
+// a CU) idle.  Both / one, us in a detection: 80
 // items (1024 x 1024, n = 64) 10.1 / 8.5, 96 (n = 128) 11.9 / 9.3, 320 (2048 x
 // 2048, n = 128) 18.3 / 16.2, 352 (2048 x 2047, n = 256) 35.1 / 32.5, but 448
 // (2048 x 3000, n = 64) 14.1 / 15.3 and 1184 (4096 x 4096, n = 128) 37.4 / 40.3.
@@ -1045,7 +1042,7 @@ constexpr long long kOneWayItems = 384;
 template <int P, typename PixT, int CAP>
 hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) {
     using C = SplitCfg<P>;
-    if constexpr (sizeof(PixT) == 1) {
+    if constexpr (sizeof(PixT) == 1 && P <= 7) {
         long long items = 0;
         for (int q = 0; q < count; ++q)
             items += (long long)((runs[q].W + C::TC - 1) / C::TC) * runs[q].blocks * C::G;
@@ -1058,17 +1055,16 @@ hipError_t launch_split_pack(const RegRun* runs, int count, hipStream_t stream) 
 // one the split kernel takes.  Measured at 4096 x 4096 (us; split, then the
 // register kernel or the two passes):
 //   8-bit:  n = 32 32.5 / 35.4, 64 30.3 / 38.6, 128 42.1 / 43.7 (15.1 / 17.2 at
-//           1024 x 1024), but 256 91 / 83, 512 131 / 109: every group of shifts
-//           loads the pixels again, a byte a lane;
+//           1024 x 1024), 256 (a direction a workgroup) 68.8 / 74.5;
 //   16-bit: n = 32 54.1 / 43.4, but 64 45.1 / 56.7, 128 50.3 / 59.0, 256 81 /
-//           116, 512 129 / 140.
-constexpr int one_pass_max(int dtype) { return dtype == 0 ? kRegMaxP : 8; }
+//           95, 512 128 / 105 alone: every group of shifts loads the pixels again.
+constexpr int kOnePassMax = 8;
 constexpr int split_min(int dtype) { return dtype == 0 ? 5 : 6; }
 
 template <int P, typename PixT, int CAP>
 hipError_t launch_one(const RegRun* runs, int count, hipStream_t stream) {
     constexpr int dtype = sizeof(PixT) == 1 ? 0 : 1;
-    if constexpr (P > one_pass_max(dtype))
+    if constexpr (P > kOnePassMax)
         return hipErrorInvalidValue;
     else if constexpr (P >= split_min(dtype))
         return launch_split_pack<P, PixT, CAP>(runs, count, stream);
@@ -1088,7 +1084,6 @@ hipError_t launch_reg_p(int p, const RegRun* runs, int count, hipStream_t stream
         case 6: return launch_one<6, PixT, CAP>(runs, count, stream);
         case 7: return launch_one<7, PixT, CAP>(runs, count, stream);
         case 8: return launch_one<8, PixT, CAP>(runs, count, stream);
-        case 9: return launch_one<9, PixT, CAP>(runs, count, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1102,6 +1097,7 @@ hipError_t launch_reg_any(int p, const RegRun* runs, int count, hipStream_t stre
 }  // namespace
 
 size_t fht_scratch_bytes(const Geometry& g, int dtype) {
+    // (bands of 256 rows no longer use theirs; callers' sizes stay what they were)
     if (g.p <= kRegMaxP) return 0;
     // [h/128 sub-blocks][2 directions][128 shifts][W]: uint16 for 8-bit pixels
     // (a 128-row line sum is at most 128 * 255), int32 for 16-bit ones
@@ -1125,7 +1121,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         r.narrow = 0;
         r.grid_mode = J.grid_mode;
         r.sub16 = 0;
-        if (g.p <= one_pass_max(J.dtype)) {
+        if (g.p <= kOnePassMax) {
             r.p = g.p;
             r.blocks = g.k;
             r.to_table = 1;
@@ -1141,7 +1137,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         runs.push_back(r);
     }
     for (int dtype = 0; dtype < 2; ++dtype) {
-        for (int p = 0; p <= one_pass_max(dtype); ++p) {
+        for (int p = 0; p <= kOnePassMax; ++p) {
             for (int gm = 0; gm < 2; ++gm) {
             std::vector<RegRun> group;
             for (const RegRun& r : runs)
@@ -1159,7 +1155,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
     std::vector<CombineJob> comb;
     for (int q = 0; q < count; ++q) {
         const Geometry& g = jobs[q].g;
-        if (g.p <= one_pass_max(jobs[q].dtype)) continue;
+        if (g.p <= kOnePassMax) continue;
         CombineJob c;
         c.sub = jobs[q].scratch;
         c.sub16 = jobs[q].dtype == 0;
@@ -1173,7 +1169,7 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         c.item0 = 0;
         comb.push_back(c);
     }
-    for (int sh = 1; sh <= 3; ++sh) {
+    for (int sh = 2; sh <= 3; ++sh) {  // bands of 512 and 1024 rows
       for (int s16 = 0; s16 < 2; ++s16) {
         std::vector<CombineJob> group;
         for (const CombineJob& c : comb)
@@ -1194,13 +1190,11 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
             TimedLaunch tl("fht_combine_kernel", stream);
             const dim3 grid((unsigned)total), block(256);
             if (s16) {
-                if (sh == 1)
-                    hipLaunchKernelGGL((fht_combine_kernel<1, uint16_t>), grid, block, 0, stream, pk);
-                else if (sh == 2)
+                if (sh == 2)
                     hipLaunchKernelGGL((fht_combine_kernel<2, uint16_t>), grid, block, 0, stream, pk);
                 else
                     hipLaunchKernelGGL((fht_combine_kernel<3, uint16_t>), grid, block, 0, stream, pk);
-            } else {  // 16-bit pixels: only bands of 512 and 1024 rows come here
+            } else {
                 if (sh == 2)
                     hipLaunchKernelGGL((fht_combine_kernel<2, int32_t>), grid, block, 0, stream, pk);
                 else
