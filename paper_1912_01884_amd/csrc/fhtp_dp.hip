@@ -169,13 +169,31 @@ __device__ __forceinline__ unsigned long long pack_key(int val, int x, int r, in
     return ((unsigned long long)(unsigned int)(val + 1) << 32) | (unsigned long long)(0xffffffffu - lin);
 }
 
+// Wave-wide maximum on DPP moves (a few cycles each; a shuffle is a round trip
+// through the LDS unit for each half): rows of 16 lanes by shifts, then rows 1 and 3
+// from the row before, then the upper half from the lower.  Lanes without a source
+// take 0, below every key.  (Shuffles: 1024 x 1024, k = 16, bound 4 40.8 against 40.0
+// us a detection, no bend limit at 2048 x 1501 73.4 against 72.2.)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long v) {
+    const unsigned int lo = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)v, CTRL,
+                                                                      ROW_MASK, 0xf, true);
+    const unsigned int hi = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)(unsigned int)(v >> 32),
+                                                                      CTRL, ROW_MASK, 0xf, true);
+    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+    return o > v ? o : v;
+}
+
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const unsigned long long o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
+    v = dpp_max_u64<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_max_u64<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_max_u64<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_max_u64<0x118, 0xf>(v);  // row_shr:8: lane 15 of a row holds the row's
+    v = dpp_max_u64<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_max_u64<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3: lane 63 holds all
+    const unsigned int lo = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)v, 63);
+    const unsigned int hi = (unsigned int)__builtin_amdgcn_readlane((int)(unsigned int)(v >> 32), 63);
+    return ((unsigned long long)hi << 32) | lo;
 }
 
 // Feasible cells (x', d') of V_{i+1}: x' in [xlo, xlo + xlen) and x' + d' in
