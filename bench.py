@@ -507,7 +507,7 @@ def summarize_trace(folder):
     starts = [q for q, e in enumerate(seq) if e[2].startswith(("fht_reg_kernel", "fht_split_kernel"))]
     for q0 in reversed(starts):
         q1 = next((q for q in range(q0, len(seq)) if seq[q][2].startswith("walk")), None)
-        if q1 is None or any(", true" in e[2] for e in seq[q0:q1 + 1]):
+        if q1 is None or any("dp_pair" in e[2] and ", 1, true, " in e[2] for e in seq[q0:q1 + 1]):
             continue  # incomplete, or a through-point query (pinned kernels)
         print("\nOne detection (the last unpinned one traced; kernels in launch order):\n")
         run = {}
