@@ -33,17 +33,17 @@ HBM_PEAK_GBPS = 8000.0
 # otherwise the traffic is unknown and reported as null.
 TRAFFIC = {
     "fht_reg_kernel": {"source": "paper_1912_01884_amd/csrc/fhtp_fht.hip",
-                      "source_sha256": "e7eee6e6575463104e02e08783cd3137e37f8275f260b872fb3e9b5f019fc535",
-                      "fetch_bytes": 36827289, "write_bytes": 142582784},
+                      "source_sha256": "9d73033e0014b16414875596cded44c0f281d34acca4925aa21fe0748633f190",
+                      "fetch_bytes": 46008000, "write_bytes": 137945907},
     "dp_pair_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-                     "source_sha256": "a6bf6ca8288b017f2832837c1fe9d972cf6ff7e6104683c978afdf24e9237859",
-                     "fetch_bytes": 13988813, "write_bytes": 6653440},
+                     "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
+                     "fetch_bytes": 13993000, "write_bytes": 6653440},
     "dp_step_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-                     "source_sha256": "a6bf6ca8288b017f2832837c1fe9d972cf6ff7e6104683c978afdf24e9237859",
-                     "fetch_bytes": 8680520, "write_bytes": 6144},
+                     "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
+                     "fetch_bytes": 8688000, "write_bytes": 6144},
     "walk": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-            "source_sha256": "a6bf6ca8288b017f2832837c1fe9d972cf6ff7e6104683c978afdf24e9237859",
-            "fetch_bytes": 67448, "write_bytes": 192},
+            "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
+            "fetch_bytes": 66340, "write_bytes": 205},
 }
 
 
