@@ -39,7 +39,7 @@ private:
     hipEvent_t begin_ = nullptr;
 };
 
-// Largest band height the register FHT kernel handles in one pass.
+// Row blocks (log2) that bands transformed in two passes are cut into.
 constexpr int kRegMaxP = 7;
 
 // ---- band tables ------------------------------------------------------------
