@@ -33,8 +33,8 @@ HBM_PEAK_GBPS = 8000.0
 # otherwise the traffic is unknown and reported as null.
 TRAFFIC = {
     "fht_reg_kernel": {"source": "paper_1912_01884_amd/csrc/fhtp_fht.hip",
-                      "source_sha256": "9d73033e0014b16414875596cded44c0f281d34acca4925aa21fe0748633f190",
-                      "fetch_bytes": 46008000, "write_bytes": 137945907},
+                      "source_sha256": "2f388ffb645cd52891ba82f421392734628ae932985defb45aee7208843c7124",
+                      "fetch_bytes": 46046000, "write_bytes": 137935974},
     "dp_pair_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
                      "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
                      "fetch_bytes": 13993000, "write_bytes": 6653440},

@@ -754,9 +754,14 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
     // Phase 1: a wave per (block, CG-th of the columns).  (The pixels of all
     // of a wave's tasks loaded before the first one's sums: 53.6 against 50.1 us
     // at 4096 x 4096, n = 128, 16-bit pixels.  The loads are not what it waits for.)
-#pragma unroll 1
-    for (int task = wave; task < C::M * C::CG; task += WAVES) {
-        const int m = task % C::M, cg = task / C::M;
+    // A wave stays with one block, so its rows' view and skews are formed once;
+    // unrolled, 78.8 -> 74.6 us at 4096 x 4096, n = 256, 16-bit, 50.8 -> 49.0 at 128.
+    static_assert(WAVES % C::M == 0, "whole rounds of the blocks");
+    const int m = wave % C::M;
+#pragma unroll
+    for (int q = 0; q < (C::M * C::CG + WAVES - 1) / WAVES; ++q) {
+        const int cg = wave / C::M + q * (WAVES / C::M);
+        if (cg >= C::CG) break;
         uint32_t px[C::ROWS * (BOTH ? 2 : 1)];
         split_load<P, BOTH, PixT>(J, it, m, it.ct + cg * C::WC, px);
         int32_t v[C::NF][1];
