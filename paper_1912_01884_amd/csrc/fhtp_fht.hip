@@ -196,7 +196,8 @@ template <int CAP>
 struct FhtPack {
     FhtJob job[CAP];
     int count;  // runs in this pack
-    int total;  // work items in this launch
+    int total;  // work items of the pack
+    int first;  // split kernel: the item of this dispatch's first workgroup
 };
 
 // The run a work item belongs to (uniform across the workgroup).
@@ -711,7 +712,7 @@ __device__ __forceinline__ void split_store(const FhtJob& J, int blk, int dir, i
     }
 }
 
-// Item of workgroup b of the launch.  Workgroup b runs on XCD b % 8; each XCD
+// Item of workgroup b of the pack.  Workgroup b runs on XCD b % 8; each XCD
 // is dealt runs of kRun items, so that those that share pixel columns meet in
 // one L2 while the chip as a whole writes along one band at a time.  (Each XCD
 // on a contiguous eighth of the items, eight bands far apart being written at
@@ -749,7 +750,7 @@ __global__ __launch_bounds__(SplitCfg<P>::NT, SplitCfg<P>::NT / 128) void fht_sp
     __shared__ int32_t fine[C::M * C::NF * C::PITCH];  // [m][f][column]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const SplitItem it = split_item<P, BOTH>(pk, (int)blockIdx.x);
+    const SplitItem it = split_item<P, BOTH>(pk, pk.first + (int)blockIdx.x);
     const FhtJob& J = pk.job[it.job];
     // Phase 1: a wave per (block, CG-th of the columns).  (The pixels of all
     // of a wave's tasks loaded before the first one's sums: 53.6 against 50.1 us
@@ -1028,12 +1029,16 @@ hipError_t launch_split_as(const RegRun* runs, int count, hipStream_t stream) {
     // One workgroup per item: its stores drain while others load (a resident
     // grid looping over the items makes an item's loads wait for the stores of
     // the one before: 57.5 against 53.9 us at 4096 x 4096, n = 128, 16 bits).
-    {
+    hipError_t e = hipSuccess;
+    for_each_dispatch(total, C::NT, [&](int first, int groups) {
+        if (e != hipSuccess) return;
+        pk.first = first;
         TimedLaunch tl("fht_reg_kernel", stream);  // one family: the band transform
-        hipLaunchKernelGGL((fht_split_kernel<P, BOTH, PixT, CAP>), dim3((unsigned)total), dim3(C::NT), 0,
+        hipLaunchKernelGGL((fht_split_kernel<P, BOTH, PixT, CAP>), dim3((unsigned)groups), dim3(C::NT), 0,
                            stream, pk);
-    }
-    return hipGetLastError();
+        e = hipGetLastError();
+    });
+    return e;
 }
 
 // 8-bit pixels: both directions in a workgroup, but one for 256-row bands (4096 x

@@ -18,6 +18,20 @@ struct Geometry {
     int pitch;  // row pitch (elements) of the DP planes: w rounded up to 64
 };
 
+// Most workgroups of `threads` threads in one dispatch: HIP refuses 2^32 threads or
+// more along x.  A multiple of 1024, so that a launch cut there keeps the order in
+// which its workgroups go to the XCDs.
+constexpr long long max_dispatch(int threads) { return 0xffffffffLL / threads / 1024 * 1024; }
+
+// Calls launch(first, count) for consecutive parts of `total` workgroups that fit
+// one dispatch each.
+template <typename F>
+inline void for_each_dispatch(long long total, int threads, F&& launch) {
+    const long long most = max_dispatch(threads);
+    for (long long first = 0; first < total; first += most)
+        launch((int)first, (int)(total - first < most ? total - first : most));
+}
+
 // Brackets a run of `launches` consecutive kernel launches of one family on
 // one stream with two events while benchmark timing is on (fhtp_timing_start);
 // a no-op otherwise, or when family is null.  Construct it right before the

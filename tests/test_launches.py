@@ -1,0 +1,39 @@
+"""Launches of whole calls at the ends of the documented ranges, without a GPU.
+
+HIP refuses a dispatch of 2^32 threads or more along x, so a launch that would
+have more is cut into several.
+"""
+
+import pytest
+
+from tests import launches
+
+LIMIT = 1 << 32
+
+
+@pytest.fixture(scope="module")
+def tmp(tmp_path_factory):
+    return tmp_path_factory.mktemp("stub")
+
+
+# (dtype, n, k, items): images whose band transform has more items of 1024
+# threads than one dispatch takes: 240 (228) columns of a band of 32 (64) rows an
+# item, of the 128-row bands a group of 64 shifts.
+@pytest.mark.parametrize("dtype,n,k,items", [(0, 32, 1024, 4370 * 1024),
+                                             (0, 64, 1000, 4600 * 1000),
+                                             (0, 128, 500, 4600 * 500 * 2),
+                                             (1, 64, 511, 4600 * 511 * 2),
+                                             (1, 128, 255, 4600 * 255 * 4)])
+def test_transform_of_the_widest_images_fits_its_dispatches(tmp, dtype, n, k, items):
+    got = launches.record(f"""
+fhtp._check(fhtp.lib().fhtp_fht_bands(PTR, {dtype}, {n * k}, {1 << 20}, {k}, PTR, PTR, 1 << 60, None),
+            "fht_bands")
+results = take()
+""", tmp)
+    assert {launches.name(m) for m, _, _ in got} == {"fht_split_kernel"}
+    assert sum(grid for _, grid, _ in got) == items
+    assert items * 1024 >= LIMIT
+    for _, grid, block in got:
+        assert block == 1024 and grid * block < LIMIT
+    # a dispatch that is not the last ends where the workgroups' order repeats
+    assert all(grid % 1024 == 0 for _, grid, _ in got[:-1])
