@@ -1144,6 +1144,9 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
             r.out = static_cast<int32_t*>(J.scratch);
             r.sub16 = J.dtype == 0;
         }
+        // Only the register kernel's grid has a choice: elsewhere it must not keep
+        // runs from sharing a launch.
+        if (r.p >= split_min(r.dtype)) r.grid_mode = 0;
         runs.push_back(r);
     }
     for (int dtype = 0; dtype < 2; ++dtype) {

@@ -37,3 +37,19 @@ results = take()
         assert block == 1024 and grid * block < LIMIT
     # a dispatch that is not the last ends where the workgroups' order repeats
     assert all(grid % 1024 == 0 for _, grid, _ in got[:-1])
+
+
+# The 128-row blocks of 512- and 1024-row bands: the split transform has no grid to
+# choose, so rules that differ in fht_grid leave them in one launch.
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_grid_rules_do_not_part_launches_without_a_grid_choice(tmp, dtype):
+    got = launches.record(f"""
+from paper_1912_01884_amd import autotune
+shapes = [(1024, 300, 2, {dtype}), (2048, 300, 2, {dtype})]
+bends = [fhtp.make_bend(3)] * 2
+for grid in (0, 1):
+    fhtp.tune_set([autotune.rule(log2n=9, fht_grid=grid)])
+    results.append(batch(shapes, bends))
+""", tmp)
+    for run in got:
+        assert [launches.name(m) for m, _, _ in run].count("fht_split_kernel") == 1
