@@ -107,6 +107,7 @@ struct DpPack {
     DpJob job[CAP];
     int count;
     int total;  // workgroups in the launch
+    int first;  // block kernel: the item of this dispatch's first workgroup
 };
 
 // One image in the walk launch.
@@ -1262,7 +1263,7 @@ __global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(
     __shared__ unsigned short wlo[ROWS], whi[ROWS];  // window of each row, as rows
     auto at = [](int r, int c) { return r * COLS + c + (r / kBlk) * COLS; };
 
-    const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
+    const int it = (CAP > 1 ? pk.first : 0) + xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     const int jj = dp_find_job(pk, it);
     const DpJob& a = pk.job[jj];
     const int local = it - a.item0;  // the column tile
@@ -1891,6 +1892,7 @@ template <int CAP>
 struct ColPack {
     ColJob job[CAP];
     int count;
+    int first;  // the item of this dispatch's first workgroup
 };
 
 __device__ __forceinline__ unsigned long long col_key(int val, int x) {
@@ -1901,7 +1903,7 @@ __device__ __forceinline__ unsigned long long col_key(int val, int x) {
 template <int COLS, typename AT, int CAP, typename TT>
 __global__ __launch_bounds__(64 * kColWaves) void dp_colmax(ColPack<CAP> pk) {
     constexpr int LANES = 64 * kColWaves / COLS;  // row lanes
-    const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
+    const int it = (CAP > 1 ? pk.first : 0) + xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     int jj = 0;
     if constexpr (CAP > 1) {
         int hi = pk.count - 1;
@@ -2222,15 +2224,18 @@ void launch_fixed_b(int dc, hipStream_t s, const DpPack<CAP>& pk) {
 }
 
 template <typename AT, int CAP, typename TT>
-hipError_t launch_step_t(const DpClass& c, hipStream_t s, const DpPack<CAP>& pk) {
+hipError_t launch_step_t(const DpClass& c, hipStream_t s, DpPack<CAP>& pk) {
     if (c.kind != (int)WindowKind::Fixed) {
         auto blocks = [&](auto rows_tag) {
             constexpr int ROWS = decltype(rows_tag)::value;
             auto tile = [&](auto cols_tag) {
                 constexpr int COLS = decltype(cols_tag)::value;
                 if constexpr (COLS <= blk_most_cols(ROWS))
-                    hipLaunchKernelGGL((dp_step_blocks<ROWS, COLS, AT, CAP, TT>), dim3(pk.total),
-                                       dim3(BlkCfg<ROWS, COLS>::THREADS), 0, s, pk);
+                    for_each_dispatch(pk.total, BlkCfg<ROWS, COLS>::THREADS, [&](int first, int groups) {
+                        pk.first = first;
+                        hipLaunchKernelGGL((dp_step_blocks<ROWS, COLS, AT, CAP, TT>), dim3(groups),
+                                           dim3(BlkCfg<ROWS, COLS>::THREADS), 0, s, pk);
+                    });
             };
             if constexpr (CAP > 1) {
                 tile(std::integral_constant<int, blk_most_cols(ROWS)>{});
@@ -2269,7 +2274,7 @@ hipError_t launch_step_t(const DpClass& c, hipStream_t s, const DpPack<CAP>& pk)
 }
 
 template <typename AT, int CAP>
-hipError_t launch_step(const DpClass& c, hipStream_t s, const DpPack<CAP>& pk) {
+hipError_t launch_step(const DpClass& c, hipStream_t s, DpPack<CAP>& pk) {
     return c.narrow ? launch_step_t<AT, CAP, uint16_t>(c, s, pk)
                     : launch_step_t<AT, CAP, int32_t>(c, s, pk);
 }
@@ -2702,13 +2707,18 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
             }
             if (cnt == 0) continue;
             pk.count = cnt;
-            const dim3 grid((unsigned)total), block(64 * kColWaves);
+            const dim3 block(64 * kColWaves);
             auto launch = [&](auto cols_tag) {
                 constexpr int COLS = decltype(cols_tag)::value;
-                if (!wide && c.narrow)
-                    hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, uint16_t>), grid, block, 0, s, pk);
-                else
-                    hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, int32_t>), grid, block, 0, s, pk);
+                for_each_dispatch(total, 64 * kColWaves, [&](int first, int groups) {
+                    pk.first = first;
+                    if (!wide && c.narrow)
+                        hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, uint16_t>), dim3(groups), block, 0,
+                                           s, pk);
+                    else
+                        hipLaunchKernelGGL((dp_colmax<COLS, AT, CAP, int32_t>), dim3(groups), block, 0,
+                                           s, pk);
+                });
             };
             if constexpr (CAP > 1) {
                 launch(std::integral_constant<int, 32>{});

@@ -18,9 +18,10 @@ struct Geometry {
     int pitch;  // row pitch (elements) of the DP planes: w rounded up to 64
 };
 
-// Most workgroups of `threads` threads in one dispatch: HIP refuses 2^32 threads or
-// more along x.  A multiple of 1024, so that a launch cut there keeps the order in
-// which its workgroups go to the XCDs.
+// Most workgroups of `threads` threads in one dispatch, which takes fewer than 2^32
+// threads along x (of a larger grid the count is kept in 32 bits: part of it runs,
+// without an error, or none, with one).  A multiple of 1024, so that a launch cut
+// there keeps the order in which its workgroups go to the XCDs.
 constexpr long long max_dispatch(int threads) { return 0xffffffffLL / threads / 1024 * 1024; }
 
 // Calls launch(first, count) for consecutive parts of `total` workgroups that fit

@@ -1,7 +1,7 @@
 """Launches of whole calls at the ends of the documented ranges, without a GPU.
 
-HIP refuses a dispatch of 2^32 threads or more along x, so a launch that would
-have more is cut into several.
+A dispatch takes fewer than 2^32 threads along x, so a launch that would have more
+is cut into several.
 """
 
 import pytest
@@ -53,3 +53,21 @@ for grid in (0, 1):
 """, tmp)
     for run in got:
         assert [launches.name(m) for m, _, _ in run].count("fht_split_kernel") == 1
+
+
+# Packs of the widest images, of few rows: 64 workgroups of 1024 threads for each 1024
+# columns of a pack's scanned windows, 32 of its column recurrence.
+@pytest.mark.parametrize("count,h,bend", [(64, 2, "fhtp.make_bend(1 << 20)"),
+                                          (65, 4, "fhtp.make_bend(None, 0.3)"),
+                                          (256, 4, "fhtp.make_bend(None, 0.3)"),
+                                          (130, 4, "fhtp.make_bend(1 << 20)"),
+                                          (256, 4, "fhtp.make_bend(1 << 20)")])
+def test_steps_of_packs_of_the_widest_images_fit_their_dispatches(tmp, count, h, bend):
+    got = launches.record(f"""
+results = batch([({h}, {1 << 20}, 2, 0)] * {count}, [{bend}] * {count})
+""", tmp)
+    for m, grid, block in got:
+        assert 0 < grid * block < LIMIT, launches.name(m)
+    steps = [(grid, block) for m, grid, block in got
+             if launches.name(m) not in ("fht_reg_kernel", "walk", "walk_colmax", "angle_windows")]
+    assert sum(grid * block for grid, block in steps) >= count * (1 << 20) * 4
