@@ -1250,27 +1250,41 @@ struct BlkCfg {
     }
 };
 
-template <int ROWS, int COLS, typename AT, int CAP, typename TT>
-__global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(DpPack<CAP> pk) {
+// A tile's arrays in LDS.  Row r of column c is at r * COLS + c, blocks COLS words
+// apart (the lanes of a wave that scan different blocks of the same columns hit
+// other banks).
+template <int ROWS, int COLS>
+struct BlkLds {
+    using C = BlkCfg<ROWS, COLS>;
+    static constexpr int NB = C::NB, LV = C::levels();
+    static constexpr int SIZE = C::CELLS + NB * COLS;
+    static constexpr int WAVES = (C::THREADS + 63) / 64;
+    // V_{i+1}(X0 + c, row r), -1 where none (and room for reads past a window)
+    int vt[SIZE + (kBlk - 1) * COLS];
+    int pre_v[SIZE];                   // max over [block start, r]
+    int suf_v[SIZE];                   // max over [r, block end]
+    int run_v[LV][NB][COLS];           // max over blocks [b, b + 2^l)
+    unsigned short run_i[LV][NB][COLS];
+    unsigned short wlo[ROWS], whi[ROWS];  // window of each row, as rows
+    unsigned char ps_i[C::CELLS];      // smallest rows of pre_v, suf_v in the block: pre, suf << 4
+    unsigned long long part[WAVES];    // the last step's best keys of the waves
+    int part_s[WAVES];
+};
+
+// Column tile `local` of image a.
+template <int ROWS, int COLS, typename AT, typename TT>
+__device__ __forceinline__ void blocks_tile(const DpJob& a, int local, BlkLds<ROWS, COLS>& m_) {
     using C = BlkCfg<ROWS, COLS>;
     constexpr int NB = C::NB, LV = C::levels();
-    // row r of column c at r * COLS + c, blocks COLS words apart (the lanes of a
-    // wave that scan different blocks of the same columns hit other banks)
-    constexpr int SIZE = C::CELLS + NB * COLS;
-    // V_{i+1}(X0 + c, row r), -1 where none (and room for reads past a window)
-    __shared__ int vt[SIZE + (kBlk - 1) * COLS];
-    __shared__ int pre_v[SIZE];                // max over [block start, r]
-    __shared__ int suf_v[SIZE];                // max over [r, block end]
-    __shared__ unsigned char ps_i[C::CELLS];   // their smallest rows in the block: pre, suf << 4
-    __shared__ int run_v[LV][NB][COLS];        // max over blocks [b, b + 2^l)
-    __shared__ unsigned short run_i[LV][NB][COLS];
-    __shared__ unsigned short wlo[ROWS], whi[ROWS];  // window of each row, as rows
+    auto& vt = m_.vt;
+    auto& pre_v = m_.pre_v;
+    auto& suf_v = m_.suf_v;
+    auto& ps_i = m_.ps_i;
+    auto& run_v = m_.run_v;
+    auto& run_i = m_.run_i;
+    auto& wlo = m_.wlo;
+    auto& whi = m_.whi;
     auto at = [](int r, int c) { return r * COLS + c + (r / kBlk) * COLS; };
-
-    const int it = (CAP > 1 ? pk.first : 0) + xcd_run_item((int)blockIdx.x, (int)gridDim.x);
-    const int jj = dp_find_job(pk, it);
-    const DpJob& a = pk.job[jj];
-    const int local = it - a.item0;  // the column tile
     const int n = a.n, w = a.w, D = 2 * n - 1;
     const int t = threadIdx.x;
     const int c = t % COLS;
@@ -1443,9 +1457,9 @@ __global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(
     }
     if (last) {
         // the workgroup's best key and that cell's successor, slot = column tile
-        constexpr int W = (C::THREADS + 63) / 64;
-        __shared__ unsigned long long part[W];
-        __shared__ int part_s[W];
+        constexpr int W = BlkLds<ROWS, COLS>::WAVES;
+        auto& part = m_.part;
+        auto& part_s = m_.part_s;
         const int lane = t & 63, wave = t >> 6;
         best = wave_best(best);
         if (lane == 0) {
@@ -1466,6 +1480,65 @@ __global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(
             a.succ[local] = ms;
         }
     }
+}
+
+// One image a launch: tiles as wide as the chip needs (blk_cols).
+template <int ROWS, int COLS, typename AT, typename TT>
+__global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(DpPack<1> pk) {
+    __shared__ BlkLds<ROWS, COLS> lds;
+    blocks_tile<ROWS, COLS, AT, TT>(pk.job[0], xcd_run_item((int)blockIdx.x, (int)gridDim.x), lds);
+}
+
+// Tile of the block kernel: the rows it holds (D < rows), and its most columns (what
+// LDS holds; 32 columns of 255 rows were slower at every width).
+__host__ __device__ constexpr int blk_rows(int D) {
+    int r = 64;
+    while (r <= D) r *= 2;
+    return r;
+}
+constexpr int blk_most_cols(int rows) {
+    return rows <= 512 ? 16 : rows == 1024 ? 8 : 4;
+}
+
+// A pack of images, of any band heights with one width of back-pointers: a workgroup
+// takes its image's tile at its most columns (1024 threads and, of the taller
+// tiles, one workgroup a CU for each of them), so that images of different heights
+// share the launches of their steps.  A chain of launches for each tile height
+// instead: 8 images of 128 to 2048 rows, 256 to 2048 columns, k = 4 to 16, 0.1 rad
+// 331 us a batch,
+// together 237; 128 such images 1882 / 1794.
+template <typename AT, typename TT>
+__global__ __launch_bounds__(1024, sizeof(AT) == 1 ? 8 : 4) void dp_step_blocks_pack(DpPack<kPack> pk) {
+    constexpr int R = sizeof(AT) == 1 ? 64 : 512;  // the smallest tile's rows
+    constexpr int C0 = blk_most_cols(R), C1 = blk_most_cols(2 * R), C2 = blk_most_cols(4 * R);
+    static_assert(BlkCfg<R, C0>::THREADS == 1024 && BlkCfg<2 * R, C1>::THREADS == 1024 &&
+                      BlkCfg<4 * R, C2>::THREADS == 1024,
+                  "one block shape");
+    __shared__ union {
+        BlkLds<R, C0> a;
+        BlkLds<2 * R, C1> b;
+        BlkLds<4 * R, C2> c;
+    } lds;
+    // Items as xcd_run_item deals them, but in runs of 32 where there are many, so that
+    // every XCD gets its share of each height (8 images of 4096 and 8192 rows, 256 to
+    // 8192 columns, 0.1 rad 4365 / 4131 us; with few, 8 mixed images as above, 240 / 259).
+    const int b = (int)blockIdx.x, grid = (int)gridDim.x;
+    constexpr int kRun = 32;
+    const int whole = grid / (kXcds * kRun) * (kXcds * kRun);
+    const int xcd = b % kXcds, slot = b / kXcds;
+    const int at = grid < 4096 ? xcd_run_item(b, grid)
+                   : b < whole ? slot / kRun * (kXcds * kRun) + xcd * kRun + slot % kRun
+                               : b;
+    const int it = pk.first + at;
+    const DpJob& a = pk.job[__builtin_amdgcn_readfirstlane(dp_find_job(pk, it))];
+    const int local = it - a.item0;  // the column tile
+    const int rows = blk_rows(2 * a.n - 1);
+    if (rows == R)
+        blocks_tile<R, C0, AT, TT>(a, local, lds.a);
+    else if (rows == 2 * R)
+        blocks_tile<2 * R, C1, AT, TT>(a, local, lds.b);
+    else
+        blocks_tile<4 * R, C2, AT, TT>(a, local, lds.c);
 }
 
 // k = 1: the answer is the best masked cell of H_0 (htab), pinned as vin.
@@ -2143,13 +2216,13 @@ struct DpClass {
     int dc;     // fixed kernels: displacements per thread
     bool a16;
     bool narrow;  // uint16 tables (bands 0 .. k-2)
-    int rows;     // scanned windows: rows of the block kernel's tile, else 0
-    int cols = 0; // and its columns (per launch)
+    bool blocks;  // scanned windows: the block kernel
+    int rows = 0, cols = 0;  // and in a launch of one image its tile (not part of the class)
     int steps;    // most DP steps per launch allowed, 1..3 (tuning)
     int stripe;   // item-order stripe of the multi-step kernels (tuning)
     bool operator==(const DpClass& o) const {
         return kind == o.kind && bound == o.bound && dc == o.dc && a16 == o.a16 &&
-               narrow == o.narrow && rows == o.rows && steps == o.steps && stripe == o.stripe;
+               narrow == o.narrow && blocks == o.blocks && steps == o.steps && stripe == o.stripe;
     }
 };
 
@@ -2172,27 +2245,16 @@ bool colmax_apply(const DpJobSpec& J) {
     return J.plan.kind == WindowKind::Full && J.pin.j < 0 && J.g.k >= 2 && J.g.D >= 3;
 }
 
-// Tile of the block kernel: the rows it holds (D < rows).
-int blk_rows(const Geometry& g) {
-    int r = 64;
-    while (r <= g.D) r *= 2;
-    return r;
-}
-
-// Its most columns (what LDS holds; 32 columns of 255 rows were slower at every
-// width), and its columns in a launch of one image: the fewest that need at most
-// one workgroup per CU.  A narrower tile shortens every phase of a launch while
+// Columns of the block kernel's tile in a launch of one image: the fewest that need
+// at most one workgroup per CU.  A narrower tile shortens every phase of a launch while
 // CUs are idle; with more than one workgroup a CU the wider row segments win.
 // Detections of 128-row bands, k = 16, 0.1 rad, 4 / 8 / 16 columns: w = 300 93 /
 // 101 / 120 us, 1500 112 / 103 / 121, 3000 158 / 129 / 129, 8000 307 / 232 / 197;
 // 511 displacements at w = 2047 101 / 94 / 114.  A pack of images keeps the most.
 // The last step writes a key per tile and takes the fewest columns whose keys fit.
-constexpr int blk_most_cols(int rows) {
-    return rows <= 512 ? 16 : rows == 1024 ? 8 : 4;
-}
 int blk_cols(const Geometry& g, bool alone, bool last) {
     constexpr int kCus = 256;  // compute units of the MI355X
-    const int most = blk_most_cols(blk_rows(g));
+    const int most = blk_most_cols(blk_rows(g.D));
     int c = most;
     if (alone)
         for (c = 4; c < most && (g.w + c - 1) / c > kCus;) c *= 2;
@@ -2211,12 +2273,13 @@ DpClass class_of(const DpJobSpec& j) {
     c.narrow = j.tables.narrow > 0;
     c.steps = j.plan.steps;
     c.stripe = j.plan.stripe;
-    c.rows = 0;
+    c.blocks = false;
     if (j.plan.kind == WindowKind::Full && colmax_apply(j)) {
         c.kind = (int)WindowKind::Full;  // the column recurrence
     } else if (!fixed) {
         c.kind = (int)WindowKind::Generic;  // the block kernel for every other kind
-        c.rows = blk_rows(j.g);
+        c.blocks = true;
+        c.rows = blk_rows(j.g.D);
     }
     return c;
 }
@@ -2244,25 +2307,25 @@ void launch_fixed_b(int dc, hipStream_t s, const DpPack<CAP>& pk) {
 template <typename AT, int CAP, typename TT>
 hipError_t launch_step_t(const DpClass& c, hipStream_t s, DpPack<CAP>& pk) {
     if (c.kind != (int)WindowKind::Fixed) {
+        if constexpr (CAP > 1) {
+            for_each_dispatch(pk.total, 1024, [&](int first, int groups) {
+                pk.first = first;
+                hipLaunchKernelGGL((dp_step_blocks_pack<AT, TT>), dim3(groups), dim3(1024), 0, s, pk);
+            });
+            return hipSuccess;
+        } else {
         auto blocks = [&](auto rows_tag) {
             constexpr int ROWS = decltype(rows_tag)::value;
             auto tile = [&](auto cols_tag) {
                 constexpr int COLS = decltype(cols_tag)::value;
                 if constexpr (COLS <= blk_most_cols(ROWS))
-                    for_each_dispatch(pk.total, BlkCfg<ROWS, COLS>::THREADS, [&](int first, int groups) {
-                        pk.first = first;
-                        hipLaunchKernelGGL((dp_step_blocks<ROWS, COLS, AT, CAP, TT>), dim3(groups),
-                                           dim3(BlkCfg<ROWS, COLS>::THREADS), 0, s, pk);
-                    });
+                    hipLaunchKernelGGL((dp_step_blocks<ROWS, COLS, AT, TT>), dim3(pk.total),
+                                       dim3(BlkCfg<ROWS, COLS>::THREADS), 0, s, pk);
             };
-            if constexpr (CAP > 1) {
-                tile(std::integral_constant<int, blk_most_cols(ROWS)>{});
-            } else {
-                switch (c.cols) {
-                    case 4: tile(std::integral_constant<int, 4>{}); break;
-                    case 8: tile(std::integral_constant<int, 8>{}); break;
-                    default: tile(std::integral_constant<int, 16>{}); break;
-                }
+            switch (c.cols) {
+                case 4: tile(std::integral_constant<int, 4>{}); break;
+                case 8: tile(std::integral_constant<int, 8>{}); break;
+                default: tile(std::integral_constant<int, 16>{}); break;
             }
         };
         if constexpr (sizeof(AT) == 1) {  // at most 256 displacements
@@ -2279,6 +2342,7 @@ hipError_t launch_step_t(const DpClass& c, hipStream_t s, DpPack<CAP>& pk) {
                 case 2048: blocks(std::integral_constant<int, 2048>{}); return hipSuccess;
                 default: return hipErrorInvalidValue;
             }
+        }
         }
     }
 #define FHTP_B(BB) \
@@ -2363,7 +2427,7 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
                 }
             }
             a.out_pin_x = J->pin.j == i ? J->pin.x : -1;
-            if (c.rows) {
+            if (c.blocks) {
                 cs.cols = blk_cols(g, CAP == 1, last);
                 a.items_x = (g.w + cs.cols - 1) / cs.cols;
                 a.items_y = 1;
@@ -2798,7 +2862,7 @@ hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs,
             a.key = J.buf.key;
             a.succ = J.buf.succ;
             a.n_keys = g.k == 1        ? (int)(((g.w + 63) / 64) * items_y_of(g, kDCGeneric))
-                       : c.rows ? (g.w + blk_cols(g, CAP == 1, true) - 1) / blk_cols(g, CAP == 1, true)
+                       : c.blocks ? (g.w + blk_cols(g, CAP == 1, true) - 1) / blk_cols(g, CAP == 1, true)
                                 : (int)(((g.w + 63) / 64) * items_y_of(g, c.dc));
             a.a_base = J.buf.a;
             a.a_plane = (size_t)g.D * g.pitch;

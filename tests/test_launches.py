@@ -71,3 +71,16 @@ results = batch([({h}, {1 << 20}, 2, 0)] * {count}, [{bend}] * {count})
     steps = [(grid, block) for m, grid, block in got
              if launches.name(m) not in ("fht_reg_kernel", "walk", "walk_colmax", "angle_windows")]
     assert sum(grid * block for grid, block in steps) >= count * (1 << 20) * 4
+
+
+# Scanned windows of every band height: a batch's images of one width of back-pointers
+# and of tables share the launches of their steps.
+@pytest.mark.parametrize("bend", ["fhtp.make_bend(None, 0.3)", "fhtp.make_bend(25)"])
+def test_heights_of_a_batch_share_their_step_launches(tmp, bend):
+    low = [(16 * 5, 200), (32 * 9, 500), (64 * 4, 333), (128 * 3, 90)]
+    tall = [(256 * 4, 70), (512 * 2, 140), (1024 * 6, 33)]
+    shapes = [(h, w, k, 1) for (h, w), k in zip(low + tall, (5, 9, 4, 3, 4, 2, 6))]
+    got = launches.record(f"results = batch({shapes}, [{bend}] * {len(shapes)})", tmp)
+    steps = [launches.name(m) for m, _, _ in got if launches.name(m).startswith("dp_step")]
+    # the longest chain of each width of back-pointers
+    assert len(steps) == (9 - 1) + (6 - 1)
