@@ -59,7 +59,7 @@ namespace {
 
 constexpr int kWaves = 4;      // waves per workgroup, one displacement chunk each
 constexpr int kMaxFixedB = 16; // largest bend bound with a register-window kernel
-constexpr int kDCGeneric = 8;  // displacements per thread in argmax_table
+constexpr int kDCGeneric = 8;  // displacements per thread in the scanning kernel and argmax_table
 constexpr int kPack = 256;     // images per launch (kernel arguments of up to 32 KB)
 constexpr int kXcds = 8;       // accelerator dies of the MI355X, each with its own L2
 
@@ -363,7 +363,45 @@ using PairLinks = std::conditional_t<sizeof(AT) == 1, uint16_t, uint32_t>;
 template <typename AT>
 constexpr int kLinkBits = 8 * (int)sizeof(AT);
 
+// Byte offset of a row inside the view (0 for rows it does not cover, whose
+// lanes are masked by an out-of-range lane offset instead).
+__device__ __forceinline__ unsigned int row_off(const RowView& v, int row, int pitch, int esz) {
+    return (row >= v.base && row < v.end) ? (unsigned int)(row - v.base) * pitch * esz : 0u;
+}
+
 constexpr unsigned int kOut = 0x80000000u;  // lane offset past every view: loads 0, stores drop
+
+// One output cell (x' = xp, displacement d) with range maximum m reached at
+// row ra, stored through the views of the wave's rows of V_i (ov) and
+// A_{i+1} (av).
+template <typename AT>
+__device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const RowView& av, int m,
+                                     int ra, int hval, int xp, int d, Best& best) {
+    const int n = a.n, w = a.w;
+    const int D = 2 * n - 1;
+    const int r = d + n - 1;
+    if (xp >= w || r >= D) return;
+    const bool last = a.key != nullptr;
+    if (!last) {
+        const unsigned int arow = row_off(av, r, a.a_pitch, sizeof(AT));
+        const unsigned int aval = (unsigned int)(ra < 0 ? 0 : ra);
+        if constexpr (sizeof(AT) == 1)
+            __builtin_amdgcn_raw_buffer_store_b8((unsigned char)aval, av.rs, xp, (int)arow,
+                                                 kStoreScope);
+        else
+            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)aval, av.rs, xp * 2, (int)arow,
+                                                  kStoreScope);
+    }
+    const int x = xp - d;
+    if (x < 0 || x >= w) return;
+    const int val = (m >= 0 && (a.out_pin_x < 0 || x == a.out_pin_x)) ? hval + m : -1;
+    if (last) {
+        take_best(best, pack_key(val, x, r, D), ra);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.v_pitch, 4),
+                                              kStoreScope);
+    }
+}
 
 // Sliding maximum of the windows [j, j + 2B] of v, j = 0 .. DC-1, with the
 // smallest index reaching it: each window is split at a block start b in
@@ -1180,6 +1218,8 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     }
 }
 
+constexpr int kEmpty = -2147483647 - 1;  // no cell yet (below every V, -1 included)
+
 // Mode-1 window of displacement d: lo and hi bracket every d' with
 // n*|d'-d| <= t*(n*n + d*d').  Both sides are exact products of integers below
 // 2^22 except the one rounding of t times the integer, so the result does not
@@ -1209,6 +1249,166 @@ __device__ __forceinline__ void angle_window(int n, double t, int d, int& lo, in
     hi = a;
 }
 
+// The scanning step: per-displacement windows [lo(d), hi(d)] as the block kernel
+// takes, for the sizes where it is the faster one (scan_alone, scan_pack).  Both window ends are non-decreasing in d, so
+// the windows of a wave's kDCGeneric displacements fall into groups that
+// share a point c (c = hi of the group's first window): each window of a
+// group is [lo, c] + [c+1, hi].  One descending scan from c gives every
+// [lo, c] maximum (recorded as the scan passes each lo) and one ascending scan
+// from c+1 gives every [c+1, hi] maximum, so each V cell of the union of the
+// windows is read and compared once, with the loads issued eight at a time.  Its
+// time is the windows' length (about 0.05 ps a cell and row beside 3.5 ps a cell at
+// 2048 x 16384 and above), in rows of 64 columns where the block kernel's tiles of
+// tall bands have 4 to 16.
+// Ties keep the smallest d' (descending scans take equal values, ascending
+// ones only larger values, and the [lo, c] part wins ties).
+constexpr int kScanTile = 8;
+
+template <typename AT, int CAP, typename TT>
+__global__ __launch_bounds__(64 * kWaves) void dp_step_generic(DpPack<CAP> pk) {
+    __shared__ int res_v[kWaves][kDCGeneric][64];
+    __shared__ int res_i[kWaves][kDCGeneric][64];
+    const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);  // as dp_step_fixed
+    const int jj = dp_find_job(pk, it);
+    const DpJob& a = pk.job[jj];
+    const int local = it - a.item0;
+    const int bx = local / a.items_y, by = local - bx * a.items_y;
+    const int n = a.n, w = a.w;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xp = bx * 64 + lane;
+    const int chunk = by * kWaves + wave;
+    const int d0 = -(n - 1) + chunk * kDCGeneric;
+    const int D = 2 * n - 1;
+    const int jn = min(kDCGeneric, D - (d0 + n - 1));  // displacements of this wave
+    const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
+    const bool last = a.key != nullptr;  // no planes to write (views unused)
+    const RowView ov = row_view(last ? a.vin : a.vout, a.v_pitch, 4, d0 + n - 1, kDCGeneric, D);
+    const RowView av = row_view(last ? a.vin : a.aout, a.a_pitch, sizeof(AT), d0 + n - 1,
+                                kDCGeneric, D);
+    int hv[kDCGeneric];
+#pragma unroll
+    for (int j = 0; j < kDCGeneric; ++j) hv[j] = load_h<TT>(a, xp, d0 + j);
+    // The wave's windows, one per lane (lanes 0 .. kDCGeneric-1), read back as
+    // scalars with readlane: no memory access inside the scans.
+    int wlo = 0, whi = 0;
+    {
+        const int dl = d0 + min(lane, kDCGeneric - 1);
+        window_of(n, a.full, a.win, a.bound, min(dl, n - 1), wlo, whi);
+    }
+    auto lo_of = [&](int j) { return __builtin_amdgcn_readlane(wlo, j); };
+    auto hi_of = [&](int j) { return __builtin_amdgcn_readlane(whi, j); };
+    if (a.full) {
+        // Section 2.2: every window is the whole column, so the workgroup's
+        // waves split the column's rows, and the smallest row reaching the
+        // maximum wins across them (ties to the lower wave).
+        __shared__ int col_v[kWaves][64];
+        __shared__ int col_i[kWaves][64];
+        const int rows = (D + kWaves - 1) / kWaves;
+        const int r_lo = wave * rows, r_hi = min(D, r_lo + rows);
+        int cv = kEmpty, ci = 0;
+        for (int t0 = r_lo; t0 < r_hi; t0 += kScanTile) {
+            int v[kScanTile];
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q)
+                v[q] = load_v(a.vin, a.vin_pitch, xp, t0 + q - (n - 1), n, mk);
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q) {
+                const bool take = t0 + q < r_hi && v[q] > cv;
+                cv = take ? v[q] : cv;
+                ci = take ? t0 + q - (n - 1) : ci;
+            }
+        }
+        col_v[wave][lane] = cv;
+        col_i[wave][lane] = ci;
+        __syncthreads();
+        int m = col_v[0][lane], ia = col_i[0][lane];
+#pragma unroll
+        for (int q = 1; q < kWaves; ++q) {
+            const bool take = col_v[q][lane] > m;
+            m = take ? col_v[q][lane] : m;
+            ia = take ? col_i[q][lane] : ia;
+        }
+        Best best;
+#pragma unroll
+        for (int j = 0; j < kDCGeneric; ++j) {
+            if (j >= jn) break;
+            emit<AT>(a, ov, av, m, ia + n - 1, hv[j], xp, d0 + j, best);
+        }
+        finish(a, best, local);
+        return;
+    }
+    for (int ja = 0; ja < jn;) {
+        const int c = hi_of(ja);
+        int jb = ja;
+        while (jb + 1 < jn && lo_of(jb + 1) <= c) ++jb;
+        // [lo_j, c], descending; record at each lo_j (j = jb down to ja)
+        const int first = lo_of(ja);
+        int cv = kEmpty, ci = c;
+        int p = jb, plo = lo_of(jb);
+        for (int t0 = c; t0 >= first; t0 -= kScanTile) {
+            int v[kScanTile];
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q) v[q] = load_v(a.vin, a.vin_pitch, xp, t0 - q, n, mk);
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q) {
+                const int dp = t0 - q;
+                if (dp < first) break;
+                const bool take = v[q] >= cv;
+                cv = take ? v[q] : cv;
+                ci = take ? dp : ci;
+                while (p >= ja && plo == dp) {
+                    res_v[wave][p][lane] = cv;
+                    res_i[wave][p][lane] = ci;
+                    --p;
+                    plo = p >= ja ? lo_of(p) : kEmpty;
+                }
+            }
+        }
+        // [c+1, hi_j], ascending; record at each hi_j (j = ja up to jb)
+        const int last = hi_of(jb);
+        cv = kEmpty;
+        ci = c;
+        p = ja;
+        int phi = hi_of(ja);
+        auto record_up = [&](int at) {
+            while (p <= jb && phi == at) {
+                const int sv = res_v[wave][p][lane];
+                const bool up = cv > sv;  // the [lo, c] part wins ties
+                res_v[wave][p][lane] = up ? cv : sv;
+                if (up) res_i[wave][p][lane] = ci;
+                ++p;
+                phi = p <= jb ? hi_of(p) : kEmpty;
+            }
+        };
+        record_up(c);
+        for (int t0 = c + 1; t0 <= last; t0 += kScanTile) {
+            int v[kScanTile];
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q) v[q] = load_v(a.vin, a.vin_pitch, xp, t0 + q, n, mk);
+#pragma unroll
+            for (int q = 0; q < kScanTile; ++q) {
+                const int dp = t0 + q;
+                if (dp > last) break;
+                const bool take = v[q] > cv;
+                cv = take ? v[q] : cv;
+                ci = take ? dp : ci;
+                record_up(dp);
+            }
+        }
+        ja = jb + 1;
+    }
+    Best best;
+#pragma unroll
+    for (int j = 0; j < kDCGeneric; ++j) {
+        if (j >= jn) break;
+        const int m = res_v[wave][j][lane];
+        const int ia = res_i[wave][j][lane];
+        emit<AT>(a, ov, av, m, ia + n - 1, hv[j], xp, d0 + j, best);
+    }
+    finish(a, best, local);
+}
+
 // Step with per-displacement windows [lo(d), hi(d)] (mode-0 bounds above the
 // fixed-window kernels', the angle form, and with a through-point pin no bound
 // at all): a workgroup owns COLS successor columns x' and every displacement
@@ -1233,8 +1433,7 @@ __device__ __forceinline__ void angle_window(int n, double t, int d, int& lo, in
 // registers and taking an interior tile's addresses from one lane offset per
 // plane took it from 8.3.  511 displacements at w = 2047: 8.3 us (a scan of every
 // window by the wave, each cell loaded once per 8 displacements: 20.8).
-constexpr int kBlk = 16;             // rows per block
-constexpr int kEmpty = -2147483647 - 1;  // no cell yet (below every V, -1 included)
+constexpr int kBlk = 16;  // rows per block
 
 template <int ROWS, int COLS>
 struct BlkCfg {
@@ -2216,7 +2415,7 @@ struct DpClass {
     int dc;     // fixed kernels: displacements per thread
     bool a16;
     bool narrow;  // uint16 tables (bands 0 .. k-2)
-    bool blocks;  // scanned windows: the block kernel
+    bool blocks;  // scanned windows: the block kernel (or, for a launch, the scanning one)
     int rows = 0, cols = 0;  // and in a launch of one image its tile (not part of the class)
     int steps;    // most DP steps per launch allowed, 1..3 (tuning)
     int stripe;   // item-order stripe of the multi-step kernels (tuning)
@@ -2263,6 +2462,68 @@ int blk_cols(const Geometry& g, bool alone, bool last) {
     return c < most ? c : most;
 }
 
+// Mean length of an image's windows, in rows (the angle form's: 2 t n at d = 0, about
+// twice that at d = n).
+double mean_window(const DpJobSpec& J) {
+    const double n = J.g.n, D = J.g.D;
+    double rows = D;
+    if (J.plan.kind == WindowKind::Angle) rows = 1.0 + 2.67 * J.plan.tan_gamma * n;
+    if (J.plan.kind == WindowKind::Generic) rows = 2.0 * J.plan.bound + 1.0;
+    return rows < D ? rows : D;
+}
+
+// Whether an image alone in its launches takes the scanning kernel: the block
+// kernel's time is its tiles', whatever the windows, and its tiles become narrower as
+// bands become taller; the scanning kernel's grows with the windows.  Measured (us
+// of steps and walk, k = 8, 4 from 512 rows; block / scan):
+//   512 rows a tile:   w = 4096 0.02 rad (15 rows) 105 / 95, 0.05 rad (35) 91 / 120;
+//                      16384 345 / 292 (4 rows), 391 / 274, 338 / 335
+//   1024:              w = 300 0.005 rad (8) 32 / 29, 2047 bound 17 (35) 44 / 48;
+//                      8192 164 / 142, bound 25 (51) 163 / 162, 40 (81) 163 / 201
+//   2048:              w = 300 bound 17 40 / 35; 4096 204 / 144, bound 40 204 / 202;
+//                      16384 838 / 735, bound 100 833 / 1287
+// The block kernel's shortest tile is mostly padding on bands of few rows, which tells
+// once the image has several workgroups a CU (and without a limit, where a scan
+// serves all rows of a column at once): 7 displacements at w = 16384 50 / 69 and at
+// 40000 105 / 71, 31 at 16384 (0.02 rad) 57 / 78 and at 40000 118 / 91, 63 at 40000
+// 123 / 118; 3 with a pin at 16384 56 / 48; 15 without a limit, with a pin, a
+// detection at 4096 41.8 / 41.1, 8192 45.4 / 40.8, 40000 148 / 50.
+bool scan_alone(const DpJobSpec& J) {
+    const Geometry& g = J.g;
+    const double w = g.w, rows = mean_window(J);
+    switch (blk_rows(g.D)) {
+        case 64:
+            if (J.plan.kind == WindowKind::Full) return g.w >= 8192;
+            return g.w >= (g.n == 2 ? 12288 : g.n == 32 ? 32768 : rows < 5.0 ? 24576 : 18432);
+        case 512: return g.w >= 4096 && rows <= 40.0 * w / (w + 2900.0);
+        case 1024: return rows <= 62.0 * w / (w + 2800.0);
+        case 2048: return rows <= std::max(35.0, 100.0 * w / (w + 1300.0));
+        default: return false;
+    }
+}
+
+// The same for a pack of images with 16-bit back-pointers, from the times those
+// figures give: 7 us a launch and 3.2 + 0.049 rows ps a cell for the scanning kernel,
+// 47, 52 and 68 ns a tile of 512, 1024 and 2048 rows for the block kernel where tiles
+// are many, and no less than a round of them.  (The margin: packs of many narrow images
+// leave more of a scan's 64 columns empty.)  128 images of 128 to 2048 rows, 256 to 2048
+// columns, bound 20 1715 us with the block kernel, 1797 scanned; 16 images of 4096
+// rows, k = 4 to 16 1298 / 1182.  The other packs keep the block kernel.
+bool scan_pack(const std::vector<const DpJobSpec*>& jobs) {
+    double scan = 7e6, tiles = 0.0, blocks = 0.0;  // ps
+    for (const DpJobSpec* J : jobs) {
+        const Geometry& g = J->g;
+        if (!J->plan.a16) return false;
+        const int rows = blk_rows(g.D);
+        const double t = (double)g.w / blk_most_cols(rows);
+        scan += (double)g.D * g.w * (3.2 + 0.049 * mean_window(*J));
+        tiles += t;
+        blocks += t * (rows == 512 ? 47e3 : rows == 1024 ? 52e3 : 68e3);
+    }
+    if (tiles < 256.0) blocks *= 256.0 / tiles;
+    return scan < 0.85 * blocks;
+}
+
 DpClass class_of(const DpJobSpec& j) {
     DpClass c;
     c.kind = (int)j.plan.kind;
@@ -2277,8 +2538,8 @@ DpClass class_of(const DpJobSpec& j) {
     if (j.plan.kind == WindowKind::Full && colmax_apply(j)) {
         c.kind = (int)WindowKind::Full;  // the column recurrence
     } else if (!fixed) {
-        c.kind = (int)WindowKind::Generic;  // the block kernel for every other kind
-        c.blocks = true;
+        c.kind = (int)WindowKind::Generic;  // scanned windows: every other kind
+        c.blocks = j.g.n > 1;  // (one-row bands would leave 63 of a tile's 64 rows idle)
         c.rows = blk_rows(j.g.D);
     }
     return c;
@@ -2286,7 +2547,9 @@ DpClass class_of(const DpJobSpec& j) {
 
 // Kernel family of a class's single-step launches (for the timing brackets).
 const char* step_family(const DpClass& c) {
-    return c.kind == (int)WindowKind::Fixed ? "dp_step_fixed" : "dp_step_blocks";
+    return c.kind == (int)WindowKind::Fixed ? "dp_step_fixed"
+           : c.blocks                       ? "dp_step_blocks"
+                                            : "dp_step_generic";
 }
 
 int items_y_of(const Geometry& g, int dc) {
@@ -2306,6 +2569,11 @@ void launch_fixed_b(int dc, hipStream_t s, const DpPack<CAP>& pk) {
 
 template <typename AT, int CAP, typename TT>
 hipError_t launch_step_t(const DpClass& c, hipStream_t s, DpPack<CAP>& pk) {
+    if (c.kind != (int)WindowKind::Fixed && !c.blocks) {
+        hipLaunchKernelGGL((dp_step_generic<AT, CAP, TT>), dim3(pk.total), dim3(64 * kWaves), 0, s,
+                           pk);
+        return hipSuccess;
+    }
     if (c.kind != (int)WindowKind::Fixed) {
         if constexpr (CAP > 1) {
             for_each_dispatch(pk.total, 1024, [&](int first, int groups) {
@@ -2368,8 +2636,9 @@ void first_step_pin(const DpJobSpec& J, int& mode, int& x) {
     x = mode ? J.pin.x : 0;
 }
 
-// Whether the angle form's windows are made by the first step's workgroups (all of
-// them, each for itself) and not by a launch of their own: up to 511 displacements
+// Whether the angle form's windows are made by the first step's workgroups of the block
+// kernel (all of them, each for itself) and not by a launch of their own: up to 511
+// displacements
 // (1024 x 1024, n = 64 81.6 against 82.7 us a detection, 511 displacements 93.4
 // against 94.2; 2047 displacements 196 against 192.5).
 bool first_step_windows(const Geometry& g) { return g.D <= 511; }
@@ -2396,6 +2665,13 @@ template <typename AT, int CAP>
 hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs, hipStream_t s) {
     int max_steps = 0;
     for (const DpJobSpec* J : jobs) max_steps = std::max(max_steps, J->g.k - 1);
+    for (const DpJobSpec* J : jobs) {
+        const Geometry& g = J->g;
+        if (J->plan.kind != WindowKind::Angle || (c.blocks && first_step_windows(g))) continue;
+        TimedLaunch tl("angle_windows", s);
+        hipLaunchKernelGGL(angle_windows, dim3((g.D + 63) / 64), dim3(64), 0, s, g.n,
+                           J->plan.tan_gamma, J->buf.win);
+    }
     TimedLaunch tl(step_family(c), s, max_steps);  // one bracket around the run of launches
     for (int st = 0; st < max_steps; ++st) {
         DpPack<CAP> pk{};
@@ -2421,7 +2697,7 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
             a.succ = last ? J->buf.succ : nullptr;
             if (st == 0) {
                 first_step_pin(*J, a.vin_pin, a.vin_pin_x);
-                if (a.win && first_step_windows(g)) {
+                if (a.win && c.blocks && first_step_windows(g)) {
                     a.win_out = J->buf.win;
                     a.tan_gamma = J->plan.tan_gamma;
                 }
@@ -2848,9 +3124,17 @@ hipError_t run_colmax_walks(const std::vector<const DpJobSpec*>& jobs, hipStream
     return hipSuccess;
 }
 
+// How an image's steps ran, where that is not what its class says: G steps a
+// launch, or the block kernel.
+struct RanAs {
+    const DpJobSpec* job;
+    int G;
+    bool blocks;
+};
+
 template <typename AT, int CAP>
-hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs,
-                     const std::vector<std::pair<const DpJobSpec*, int>>& grouped, hipStream_t s) {
+hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs, const std::vector<RanAs>& ran,
+                     hipStream_t s) {
     for (size_t q0 = 0; q0 < jobs.size(); q0 += CAP) {
         WalkPack<CAP> pk{};
         const int cnt = (int)std::min<size_t>(CAP, jobs.size() - q0);
@@ -2861,8 +3145,11 @@ hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs,
             WalkJob& a = pk.job[q];
             a.key = J.buf.key;
             a.succ = J.buf.succ;
-            a.n_keys = g.k == 1        ? (int)(((g.w + 63) / 64) * items_y_of(g, kDCGeneric))
-                       : c.blocks ? (g.w + blk_cols(g, CAP == 1, true) - 1) / blk_cols(g, CAP == 1, true)
+            RanAs how{&J, 1, false};
+            for (const RanAs& e : ran)
+                if (e.job == &J) how = e;
+            a.n_keys = g.k == 1     ? (int)(((g.w + 63) / 64) * items_y_of(g, kDCGeneric))
+                       : how.blocks ? (g.w + blk_cols(g, CAP == 1, true) - 1) / blk_cols(g, CAP == 1, true)
                                 : (int)(((g.w + 63) / 64) * items_y_of(g, c.dc));
             a.a_base = J.buf.a;
             a.a_plane = (size_t)g.D * g.pitch;
@@ -2878,9 +3165,7 @@ hipError_t run_walks(const std::vector<const DpJobSpec*>& jobs,
             // run_steps_grouped with G = 2 makes bands 1 .. P - (P & 1) in
             // pairs, P = k - 2; with G = 3 bands 1 .. 3(P / 3) in triples and,
             // when two bands are left over, those two as a pair
-            int G = 1;
-            for (const auto& e : grouped)
-                if (e.first == &J) G = e.second;
+            const int G = how.G;
             const int P = g.k - 2;
             a.tri_top = G == 3 ? 3 * (P / 3) : 0;
             a.pair_lo = G == 3 ? a.tri_top + 1 : 1;
@@ -2930,7 +3215,7 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
     for (const DpJobSpec* J : jobs)
         if (J->g.k >= 2) rest.push_back(J);
     std::vector<bool> done(rest.size(), false);
-    std::vector<std::pair<const DpJobSpec*, int>> grouped;  // images whose steps went G per launch
+    std::vector<RanAs> ran;
     std::vector<const DpJobSpec*> colmax, walked;  // the column recurrence, the others
     for (size_t q = 0; q < rest.size(); ++q) {
         if (done[q]) continue;
@@ -2960,11 +3245,13 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
                 kmax = std::max(kmax, J->g.k);
             }
             const int G = all3 && kmax >= 5 ? 3 : all2 && kmax >= 4 ? 2 : 1;
+            DpClass cp = c;  // with the pack's kernel
+            if (c.blocks) cp.blocks = !(CAP == 1 ? scan_alone(*pack[0]) : scan_pack(pack));
             hipError_t e = G > 1 ? run_steps_grouped<AT, CAP>(c, G, pack, s)
-                                 : run_steps<AT, CAP>(c, pack, s);
+                                 : run_steps<AT, CAP>(cp, pack, s);
             if (e != hipSuccess) return e;
-            if (G > 1)
-                for (const DpJobSpec* J : pack) grouped.emplace_back(J, G);
+            if (G > 1 || cp.blocks)
+                for (const DpJobSpec* J : pack) ran.push_back(RanAs{J, G, cp.blocks});
         }
     }
     for (const DpJobSpec* J : jobs)
@@ -2973,7 +3260,7 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
         hipError_t e = run_colmax_walks<AT, CAP>(colmax, s);
         if (e != hipSuccess) return e;
     }
-    return run_walks<AT, CAP>(walked, grouped, s);
+    return run_walks<AT, CAP>(walked, ran, s);
 }
 
 }  // namespace
@@ -3004,11 +3291,6 @@ hipError_t launch_dp_jobs(const DpJobSpec* jobs, int count, hipStream_t s) {
         if (J.plan.kind == WindowKind::Fixed &&
             (J.plan.bound < 0 || J.plan.bound > kMaxFixedB || (J.plan.dc != 8 && J.plan.dc != 16)))
             return hipErrorInvalidValue;
-        if (J.plan.kind == WindowKind::Angle && J.g.k >= 2 && !first_step_windows(J.g)) {
-            TimedLaunch tl("angle_windows", s);
-            hipLaunchKernelGGL(angle_windows, dim3((J.g.D + 63) / 64), dim3(64), 0, s, J.g.n,
-                               J.plan.tan_gamma, J.buf.win);
-        }
         (J.plan.a16 ? a16 : a8).push_back(&J);
     }
     hipError_t e = hipSuccess;

@@ -1,0 +1,88 @@
+"""The scanning kernel at the sizes that take it: one-row bands, bands of few rows in
+wide images, tall bands under short windows, with and without a through-point pin, and
+packs of tall bands.  Everything is integer, so results equal the oracle's.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import announce, general_path, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return require_gpu()
+
+
+def _check(dev, img, k, pin=None, **bend):
+    from paper_1912_01884_amd import fhtp
+    announce(f"{img.shape} {img.dtype} k={k} {bend} pin={pin}")
+    dimg = torch.from_numpy(img).to(dev)
+    with general_path():
+        if pin is None:
+            score, xs = fhtp.detect_polyline(dimg, k, **bend)
+            want, want_x = oracle.detect_polyline(img, k, **bend)
+        else:
+            score, xs = fhtp.detect_polyline_ex(dimg, k, pin=pin, **bend)
+            want, want_x = oracle.detect_ex(img, k, pin=pin, **bend)
+    assert int(score.cpu()[0]) == want
+    assert np.array_equal(xs.cpu().numpy(), want_x)
+
+
+CASES = [(1, 1, 5), (1, 63, 5), (1, 64, 4), (1, 4097, 9), (2, 12288, 4), (8, 24577, 3),
+         (16, 18500, 3), (32, 32768, 3), (256, 4096, 3), (512, 300, 3), (512, 4097, 2),
+         (1024, 65, 3), (1024, 300, 2)]
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+@pytest.mark.parametrize("n,w,k", CASES)
+def test_scanned(dev, n, w, k, dtype):
+    rng = np.random.default_rng(n + w)
+    img = rng.integers(0, 3 if w % 2 else 256, size=(k * n, w)).astype(dtype)
+    for gamma in (2.0 / (2.67 * n), 6.0 / (2.67 * n), min(0.3, 12.0 / n)):
+        _check(dev, img, k, gamma=gamma)
+        _check(dev, img, k, pin=(1, w // 2), gamma=gamma)
+    if n > 16:
+        _check(dev, img, k, bend=17)
+        _check(dev, img, k, pin=(k, w - 1), bend=17)
+    if n <= 32:
+        _check(dev, img, k, pin=(0, w // 3), bend=10**6)
+
+
+def test_one_row_bands_in_a_batch(dev):
+    from paper_1912_01884_amd import fhtp
+    rng = np.random.default_rng(3)
+    shapes = [(1, 900, 40), (1, 65, 9), (4, 700, 5), (1, 3000, 17)]
+    imgs = [rng.integers(0, 256, size=(n * k, w)).astype(np.uint8) for n, w, k in shapes]
+    ks = [k for _, _, k in shapes]
+    announce("batch of one-row bands")
+    with general_path():
+        got = fhtp.detect_batch([torch.from_numpy(i).to(dev) for i in imgs], ks, gammas=[0.2] * 4)
+        torch.cuda.synchronize()
+    for img, k, (score, xs) in zip(imgs, ks, got):
+        want, want_x = oracle.detect_polyline(img, k, gamma=0.2)
+        assert int(score.cpu()[0]) == want
+        assert np.array_equal(xs.cpu().numpy(), want_x)
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+@pytest.mark.parametrize("bend", [dict(bend=17), dict(gamma=0.004)])
+def test_pack_of_tall_bands(dev, dtype, bend):
+    from paper_1912_01884_amd import fhtp
+    rng = np.random.default_rng(4)
+    shapes = [(1024, 300, 3), (1024, 65, 2), (512, 333, 4), (256, 129, 5)]
+    imgs = [rng.integers(0, 9, size=(n * k, w)).astype(dtype) for n, w, k in shapes]
+    ks = [k for _, _, k in shapes]
+    announce(f"pack of tall bands {bend}")
+    got = fhtp.detect_batch([torch.from_numpy(i).to(dev) for i in imgs], ks,
+                            bends=[bend.get("bend", 0)] * 4,
+                            gammas=[bend["gamma"]] * 4 if "gamma" in bend else None)
+    torch.cuda.synchronize()
+    for img, k, (score, xs) in zip(imgs, ks, got):
+        want, want_x = oracle.detect_polyline(img, k, **bend)
+        assert int(score.cpu()[0]) == want
+        assert np.array_equal(xs.cpu().numpy(), want_x)

@@ -84,3 +84,40 @@ def test_heights_of_a_batch_share_their_step_launches(tmp, bend):
     steps = [launches.name(m) for m, _, _ in got if launches.name(m).startswith("dp_step")]
     # the longest chain of each width of back-pointers
     assert len(steps) == (9 - 1) + (6 - 1)
+
+
+# Which kernel takes an image's scanned windows, on both sides of each line.
+@pytest.mark.parametrize("n,w,bend,pin,scan", [
+    (1, 3000, "fhtp.make_bend(5)", True, True),
+    (2, 12287, "fhtp.make_bend(None, 0.3)", True, False),
+    (2, 12288, "fhtp.make_bend(None, 0.3)", True, True),
+    (16, 18431, "fhtp.make_bend(None, 0.3)", False, False),
+    (16, 18432, "fhtp.make_bend(None, 0.3)", False, True),
+    (16, 24575, "fhtp.make_bend(None, 0.02)", False, False),
+    (16, 24576, "fhtp.make_bend(None, 0.02)", True, True),
+    (32, 32767, "fhtp.make_bend(17)", False, False),
+    (32, 32768, "fhtp.make_bend(17)", False, True),
+    (32, 8191, "fhtp.make_bend(1 << 20)", True, False),
+    (32, 8192, "fhtp.make_bend(1 << 20)", True, True),
+    (64, 60000, "fhtp.make_bend(None, 0.02)", False, False),
+    (64, 60000, "fhtp.make_bend(1 << 20)", True, False),
+    (256, 4095, "fhtp.make_bend(None, 0.005)", False, False),
+    (256, 4096, "fhtp.make_bend(None, 0.005)", False, True),
+    (256, 16384, "fhtp.make_bend(17)", False, False),
+    (512, 8192, "fhtp.make_bend(17)", True, True),
+    (512, 8192, "fhtp.make_bend(40)", False, False),
+    (1024, 300, "fhtp.make_bend(17)", False, True),
+    (1024, 300, "fhtp.make_bend(18)", False, False),
+    (1024, 16384, "fhtp.make_bend(40)", False, True),
+    (1024, 16384, "fhtp.make_bend(60)", False, False),
+    (1024, 16384, "fhtp.make_bend(1 << 20)", True, False),
+])
+def test_kernel_of_scanned_windows(tmp, n, w, bend, pin, scan):
+    opt = "fhtp.make_options(pin=(1, 5))" if pin else "None"
+    got = launches.record(f"results = detect({3 * n}, {w}, 3, 1, {bend}, {opt})", tmp)
+    names = [launches.name(m) for m, _, _ in got]
+    steps = [m for m in names if m.startswith("dp_step")]
+    assert steps == ["dp_step_generic" if scan else "dp_step_blocks"] * 2
+    # the block kernel's first step makes the windows of up to 511 displacements
+    angle = "None, " in bend
+    assert names.count("angle_windows") == (1 if angle and (scan or n > 256) else 0)
