@@ -3009,19 +3009,24 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
     return launch_step<AT, CAP>(c, s, pk);
 }
 
-// Columns of a workgroup of the column recurrence: as blk_cols, the fewest that
-// need at most one workgroup per CU, at most 32.  Detections without a bend
-// limit, 8 / 16 / 32 / 64 columns: 2048 x 1501, k = 16 73.6 / 73.8 / 78.7 / 94.8 us;
-// 4096 x 4096, k = 32 194 / 180 / 185 / 220; 2048 x 8000, k = 16 146 / 106 / 101 /
-// 118.  A pack of images keeps 32.  The last step writes a key per tile and takes
-// the fewest columns whose keys fit.
-int col_cols(const Geometry& g, bool alone, bool last) {
+// Columns of a workgroup of the column recurrence in launches of `columns` columns
+// in all: the fewest that need at most one workgroup per CU, 64 (a wave's row of
+// them) at most.  us without a bend limit: detections of 16-bit images at 8 / 16 / 32
+// / 64 columns, 2048 x 1501, k = 16 73.6 / 73.8 / 78.7 / 94.8, 4096 x 4096, k = 32
+// 194 / 180 / 185 / 220, 2048 x 8000, k = 16 146 / 106 / 101 / 118; steps and walk at
+// 32 / 64, k = 8, 1024 x 12000 45.6 / 43.2, 1024 x 32768 120 / 87, 512 x 24000 51 / 43.
+// A pack of images takes 32 or 64 by all of its columns (16 images 1024 x 2000, k = 16
+// 202 / 170).
+int col_cols(long long columns, bool alone) {
     constexpr int kCus = 256;
-    int c = 32;
-    if (alone)
-        for (c = 8; c < 32 && (g.w + c - 1) / c > kCus;) c *= 2;
-    if (last)
-        while (c < 32 && (size_t)((g.w + c - 1) / c) > dp_key_count(g)) c *= 2;
+    int c = alone ? 8 : 32;
+    while (c < 64 && (columns + c - 1) / c > kCus) c *= 2;
+    return c;
+}
+
+// The last step writes a key per tile: the fewest columns, from c up, whose keys fit.
+int col_cols_last(const Geometry& g, int c) {
+    while (c < 64 && (size_t)((g.w + c - 1) / c) > dp_key_count(g)) c *= 2;
     return c;
 }
 
@@ -3032,7 +3037,8 @@ int col_cols(const Geometry& g, bool alone, bool last) {
 // reads an int32 table and the others its narrow ones when it has them, so a
 // launch splits into a pack of each where both occur.
 template <typename AT, int CAP>
-hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& jobs, hipStream_t s) {
+hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& jobs, int steps_cols,
+                      hipStream_t s) {
     int Q = 0;
     for (const DpJobSpec* J : jobs) Q = std::max(Q, J->g.k);
     TimedLaunch tl("dp_colmax", s, Q);
@@ -3041,7 +3047,7 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
         for (int wide = 1; wide >= 0; --wide) {
             ColPack<CAP> pk{};
             long long total = 0;
-            int cnt = 0, cols = 32;
+            int cnt = 0, cols = steps_cols;
             for (const DpJobSpec* J : jobs) {
                 const Geometry& g = J->g;
                 if (g.k <= i) continue;
@@ -3058,7 +3064,7 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
                 a.n = g.n;
                 a.w = g.w;
                 a.item0 = (int)total;
-                cols = col_cols(g, CAP == 1, i == 0);
+                if (CAP == 1 && i == 0) cols = col_cols_last(g, cols);
                 total += (g.w + cols - 1) / cols;
                 if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
                 pk.job[cnt++] = a;
@@ -3078,14 +3084,15 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
                                            s, pk);
                 });
             };
-            if constexpr (CAP > 1) {
+            if (cols == 64) {
+                launch(std::integral_constant<int, 64>{});
+            } else if (cols == 32) {
                 launch(std::integral_constant<int, 32>{});
-            } else {
-                switch (cols) {
-                    case 8: launch(std::integral_constant<int, 8>{}); break;
-                    case 16: launch(std::integral_constant<int, 16>{}); break;
-                    default: launch(std::integral_constant<int, 32>{}); break;
-                }
+            } else if constexpr (CAP == 1) {
+                if (cols == 16)
+                    launch(std::integral_constant<int, 16>{});
+                else
+                    launch(std::integral_constant<int, 8>{});
             }
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
@@ -3094,21 +3101,27 @@ hipError_t run_colmax(const DpClass& c, const std::vector<const DpJobSpec*>& job
     return hipSuccess;
 }
 
+// An image whose steps ran as the column recurrence, and the columns of its last
+// step's workgroups.
+struct ColRan {
+    const DpJobSpec* job;
+    int cols;
+};
+
 template <typename AT, int CAP>
-hipError_t run_colmax_walks(const std::vector<const DpJobSpec*>& jobs, hipStream_t s) {
+hipError_t run_colmax_walks(const std::vector<ColRan>& jobs, hipStream_t s) {
     for (size_t q0 = 0; q0 < jobs.size(); q0 += CAP) {
         ColWalkPack<CAP> pk{};
         const int cnt = (int)std::min<size_t>(CAP, jobs.size() - q0);
         for (int q = 0; q < cnt; ++q) {
-            const DpJobSpec& J = *jobs[q0 + q];
+            const DpJobSpec& J = *jobs[q0 + q].job;
             ColWalkJob& a = pk.job[q];
             a.key = J.buf.key;
             a.b_base = J.buf.a;
             a.score = J.score;
             a.xs = J.xs;
             a.b_pitch = J.g.pitch;
-            const int cols = col_cols(J.g, CAP == 1, true);
-            a.n_keys = (J.g.w + cols - 1) / cols;
+            a.n_keys = (J.g.w + jobs[q0 + q].cols - 1) / jobs[q0 + q].cols;
             a.n = J.g.n;
             a.w = J.g.w;
             a.k = J.g.k;
@@ -3216,7 +3229,8 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
         if (J->g.k >= 2) rest.push_back(J);
     std::vector<bool> done(rest.size(), false);
     std::vector<RanAs> ran;
-    std::vector<const DpJobSpec*> colmax, walked;  // the column recurrence, the others
+    std::vector<ColRan> colmax;
+    std::vector<const DpJobSpec*> walked;  // the others
     for (size_t q = 0; q < rest.size(); ++q) {
         if (done[q]) continue;
         const DpClass c = class_of(*rest[q]);
@@ -3230,9 +3244,13 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
             std::vector<const DpJobSpec*> pack(group.begin() + q0,
                                                group.begin() + std::min(group.size(), q0 + CAP));
             if (c.kind == (int)WindowKind::Full) {
-                hipError_t e = run_colmax<AT, CAP>(c, pack, s);
+                long long columns = 0;
+                for (const DpJobSpec* J : pack) columns += J->g.w;
+                const int cols = col_cols(columns, CAP == 1);
+                hipError_t e = run_colmax<AT, CAP>(c, pack, cols, s);
                 if (e != hipSuccess) return e;
-                colmax.insert(colmax.end(), pack.begin(), pack.end());
+                for (const DpJobSpec* J : pack)
+                    colmax.push_back(ColRan{J, CAP == 1 ? col_cols_last(J->g, cols) : cols});
                 continue;
             }
             // G steps per launch when every image qualifies and one has a
@@ -3255,7 +3273,8 @@ hipError_t launch_dp_jobs_t(const std::vector<const DpJobSpec*>& jobs, hipStream
         }
     }
     for (const DpJobSpec* J : jobs)
-        if (std::find(colmax.begin(), colmax.end(), J) == colmax.end()) walked.push_back(J);
+        if (std::none_of(colmax.begin(), colmax.end(), [&](const ColRan& r) { return r.job == J; }))
+            walked.push_back(J);
     if (!colmax.empty()) {
         hipError_t e = run_colmax_walks<AT, CAP>(colmax, s);
         if (e != hipSuccess) return e;

@@ -121,3 +121,16 @@ def test_kernel_of_scanned_windows(tmp, n, w, bend, pin, scan):
     # the block kernel's first step makes the windows of up to 511 displacements
     angle = "None, " in bend
     assert names.count("angle_windows") == (1 if angle and (scan or n > 256) else 0)
+
+
+# The column recurrence: the fewest columns a workgroup that fill the chip at most once,
+# 64 where even they do more, by the columns of the whole launch in a batch.
+@pytest.mark.parametrize("w,count,cols", [(2048, 1, 8), (2049, 1, 16), (4097, 1, 32), (8192, 1, 32),
+                                          (8193, 1, 64), (100000, 1, 64), (1000, 8, 32),
+                                          (1000, 9, 64)])
+def test_columns_of_the_recurrence(tmp, w, count, cols):
+    call = (f"detect(256, {w}, 2, 1, fhtp.make_bend(1 << 20))" if count == 1 else
+            f"batch([(256, {w}, 2, 1)] * {count}, [fhtp.make_bend(1 << 20)] * {count})")
+    got = launches.record(f"results = {call}", tmp)
+    grids = [grid for m, grid, _ in got if launches.name(m) == "dp_colmax"]
+    assert grids == [count * -(-w // cols)] * 2
