@@ -85,13 +85,18 @@ struct DpJob {
     void* aout;               // A_{i+1} plane (null on the last step)
     unsigned long long* key;  // last step: one packed key per workgroup, else null
     int32_t* succ;            // last step: per key, the row of that cell's best successor
-    const int32_t* win;       // mode-1 windows lo[D], hi[D], or null
-    int32_t* win_out;         // the image's first step makes them here, else null
-    double tan_gamma;
-    int vin_pitch, h_pitch, v_pitch, a_pitch;
+    int32_t* win;             // mode-1 windows lo[D], hi[D], or null
+    union {
+        struct {
+            int bound;  // mode-0 bound (scanned windows)
+            int full;   // windows cover every displacement
+        };
+        double tan_gamma;  // of a step that makes the mode-1 windows
+    };
+    int vin_pitch, h_pitch;
+    int pitch;    // of V_i and A_{i+1}
     int n, w;
-    int bound;    // mode-0 bound (block kernel)
-    int full;     // windows cover every displacement
+    int make_win; // the image's first step makes win
     int items_x;  // workgroups along x
     int items_y;  // workgroups along the displacements
     int item0;    // first workgroup of this image in the launch
@@ -109,6 +114,8 @@ struct DpPack {
     int total;  // workgroups in the launch
     int first;  // block kernel: the item of this dispatch's first workgroup
 };
+// (a pack's arguments go to the device with every launch)
+static_assert(sizeof(DpPack<kPack>) <= 32 * 1024, "arguments of a pack of images");
 
 // One image in the walk launch.
 struct WalkJob {
@@ -383,7 +390,7 @@ __device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const Ro
     if (xp >= w || r >= D) return;
     const bool last = a.key != nullptr;
     if (!last) {
-        const unsigned int arow = row_off(av, r, a.a_pitch, sizeof(AT));
+        const unsigned int arow = row_off(av, r, a.pitch, sizeof(AT));
         const unsigned int aval = (unsigned int)(ra < 0 ? 0 : ra);
         if constexpr (sizeof(AT) == 1)
             __builtin_amdgcn_raw_buffer_store_b8((unsigned char)aval, av.rs, xp, (int)arow,
@@ -398,7 +405,7 @@ __device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const Ro
     if (last) {
         take_best(best, pack_key(val, x, r, D), ra);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.v_pitch, 4),
+        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.pitch, 4),
                                               kStoreScope);
     }
 }
@@ -558,14 +565,14 @@ __device__ __forceinline__ Best fixed_interior(const DpJob& a, int X0, int r0, i
         }
         return best;
     }
-    const unsigned int op = (unsigned int)a.v_pitch * 4u;
-    const unsigned int ap = (unsigned int)a.a_pitch * sizeof(AT);
+    const unsigned int op = (unsigned int)a.pitch * 4u;
+    const unsigned int ap = (unsigned int)a.pitch * sizeof(AT);
     // the V_i cells lie on the same diagonal as the table cells, at 4 bytes a cell
     const unsigned int vdiag = (unsigned int)(xp - d0 - (DC - 1)) * 4u;
     const __amdgpu_buffer_rsrc_t orr = __builtin_amdgcn_make_buffer_rsrc(
-        a.vout + (size_t)r0 * a.v_pitch, (short)0, (int)(DC * op), 0x00020000);
+        a.vout + (size_t)r0 * a.pitch, (short)0, (int)(DC * op), 0x00020000);
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-        static_cast<AT*>(a.aout) + (size_t)r0 * a.a_pitch, (short)0, (int)(DC * ap), 0x00020000);
+        static_cast<AT*>(a.aout) + (size_t)r0 * a.pitch, (short)0, (int)(DC * ap), 0x00020000);
 #pragma unroll
     for (int j = 0; j < DC; ++j) {
         const int val = m[j] >= 0 ? hv[j] + m[j] : -1;
@@ -643,10 +650,10 @@ __device__ __forceinline__ Best fixed_general(const DpJob& a, int X0, int r0, in
         }
         return best;
     }
-    const RowView aview = row_view(a.aout, a.a_pitch, esz, r0, DC, D);
-    const RowView oview = row_view(a.vout, a.v_pitch, 4, r0, DC, D);
-    const unsigned int ap = (unsigned int)a.a_pitch * (unsigned int)esz;
-    const unsigned int op = (unsigned int)a.v_pitch * 4u;
+    const RowView aview = row_view(a.aout, a.pitch, esz, r0, DC, D);
+    const RowView oview = row_view(a.vout, a.pitch, 4, r0, DC, D);
+    const unsigned int ap = (unsigned int)a.pitch * (unsigned int)esz;
+    const unsigned int op = (unsigned int)a.pitch * 4u;
     const unsigned int ab = (unsigned int)(r0 - aview.base) * ap + (unsigned int)xp * (unsigned int)esz;
     const unsigned int ob = (unsigned int)(r0 - oview.base) * op + (unsigned int)xj * 4u;
 #pragma unroll
@@ -1283,8 +1290,8 @@ __global__ __launch_bounds__(64 * kWaves) void dp_step_generic(DpPack<CAP> pk) {
     const int jn = min(kDCGeneric, D - (d0 + n - 1));  // displacements of this wave
     const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
     const bool last = a.key != nullptr;  // no planes to write (views unused)
-    const RowView ov = row_view(last ? a.vin : a.vout, a.v_pitch, 4, d0 + n - 1, kDCGeneric, D);
-    const RowView av = row_view(last ? a.vin : a.aout, a.a_pitch, sizeof(AT), d0 + n - 1,
+    const RowView ov = row_view(last ? a.vin : a.vout, a.pitch, 4, d0 + n - 1, kDCGeneric, D);
+    const RowView av = row_view(last ? a.vin : a.aout, a.pitch, sizeof(AT), d0 + n - 1,
                                 kDCGeneric, D);
     int hv[kDCGeneric];
 #pragma unroll
@@ -1556,13 +1563,13 @@ __device__ __forceinline__ void blocks_tile(const DpJob& a, int local, BlkLds<RO
     }
     for (int r = t; r < D; r += C::THREADS) {
         int lo, hi;
-        if (a.win_out) {
+        if (a.make_win) {
             // the first step makes the angle form's windows for itself, and one
             // of its workgroups leaves them to later launches
             angle_window(n, a.tan_gamma, r - (n - 1), lo, hi);
             if (local == 0) {
-                a.win_out[r] = lo;
-                a.win_out[D + r] = hi;
+                a.win[r] = lo;
+                a.win[D + r] = hi;
             }
         } else {
             window_of(n, a.full, a.win, a.bound, r - (n - 1), lo, hi);
@@ -1651,8 +1658,8 @@ __device__ __forceinline__ void blocks_tile(const DpJob& a, int local, BlkLds<RO
             if ((unsigned)x < (unsigned)w) take_best(best, pack_key(val, x, r, D), ia);
             continue;
         }
-        (static_cast<AT*>(a.aout) + (size_t)r * a.a_pitch)[xp] = (AT)ia;
-        if ((unsigned)x < (unsigned)w) (a.vout + (size_t)r * a.v_pitch)[x] = val;
+        (static_cast<AT*>(a.aout) + (size_t)r * a.pitch)[xp] = (AT)ia;
+        if ((unsigned)x < (unsigned)w) (a.vout + (size_t)r * a.pitch)[x] = val;
     }
     if (last) {
         // the workgroup's best key and that cell's successor, slot = column tile
@@ -2653,8 +2660,7 @@ DpJob base_job(const DpJobSpec& J) {
     a.full = J.plan.kind == WindowKind::Full;
     a.win = J.plan.kind == WindowKind::Angle ? J.buf.win : nullptr;
     a.h_pitch = g.W;
-    a.v_pitch = g.pitch;
-    a.a_pitch = g.pitch;
+    a.pitch = g.pitch;
     a.items_x = (g.w + 63) / 64;
     a.out_pin_x = -1;
     return a;
@@ -2698,7 +2704,7 @@ hipError_t run_steps(const DpClass& c, const std::vector<const DpJobSpec*>& jobs
             if (st == 0) {
                 first_step_pin(*J, a.vin_pin, a.vin_pin_x);
                 if (a.win && c.blocks && first_step_windows(g)) {
-                    a.win_out = J->buf.win;
+                    a.make_win = 1;
                     a.tan_gamma = J->plan.tan_gamma;
                 }
             }
