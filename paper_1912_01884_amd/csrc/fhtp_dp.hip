@@ -755,7 +755,8 @@ struct DpPairJob {
     void* a;
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w, items_x, items_y;
-    int item0;  // first workgroup of this image in the launch
+    int item0;   // first workgroup of this image in the launch
+    int stripe;  // column tiles per stripe of the item order
     // Through-point pin: on the cells read from vin (the table H_{k-1} read as
     // V_{k-1}: 0 none, 1 x'' == pin, 2 x'' + d'' == pin), and on the cells of
     // V_{i+1} (pin1_x) and V_i (pin0_x) made here (-1: none).
@@ -768,7 +769,6 @@ template <int CAP>
 struct DpPairPack {
     DpPairJob job[CAP];
     int count;
-    int stripe;   // column tiles per stripe of the item order
     int through;  // write V_i through to memory (see kThroughBytes)
 };
 
@@ -797,7 +797,7 @@ __global__ __launch_bounds__((64 * PairShape<SMALL>::WAVES)) void dp_pair_fixed(
     __shared__ AT nxt[NS * STRIP][LWP];   // row of that cell's window maximum (its choice)
 
     // Workgroup b runs on XCD b % 8.  Each XCD gets a contiguous run of items
-    // instead, an image's items in stripes of pk.stripe column tiles (every
+    // instead, an image's items in stripes of a.stripe column tiles (every
     // row group of a stripe before the next stripe), so that the overlapping
     // reads of neighbouring workgroups (the widened rows, a strip's extra
     // columns, the diagonal shift between row groups) meet in one L2.
@@ -819,7 +819,7 @@ __global__ __launch_bounds__((64 * PairShape<SMALL>::WAVES)) void dp_pair_fixed(
     int bx, by;
     {
         const int local = CAP > 1 ? it - a.item0 : it;  // one image: item0 is 0
-        const int stripe = pk.stripe;
+        const int stripe = a.stripe;
         const int per_stripe = stripe * a.items_y;
         const int st = local / per_stripe, loc = local - st * per_stripe;
         const int sw = min(stripe, a.items_x - st * stripe);
@@ -995,14 +995,14 @@ struct DpTripleJob {
     void* a0;            // A_{i+1} plane: the cell's own choice
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w, items_x, items_y;
-    int item0;  // first workgroup of this image in the launch
+    int item0;   // first workgroup of this image in the launch
+    int stripe;  // column tiles per stripe of the item order
 };
 
 template <int CAP>
 struct DpTriplePack {
     DpTripleJob job[CAP];
     int count;
-    int stripe;  // column tiles per stripe of the item order
 };
 
 template <int B, typename AT, int CAP, typename TT>
@@ -1030,7 +1030,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     __shared__ AT nx2[NS1 * kStrip][LWP];   // its choice's choice (a row of V_{i+3})
 
     // Item order as in dp_pair_fixed: contiguous runs per XCD, walked in
-    // stripes of pk.stripe column tiles.
+    // stripes of a.stripe column tiles.
     const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     int jj = 0;
     if constexpr (CAP > 1) {
@@ -1049,7 +1049,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     int bx, by;
     {
         const int local = CAP > 1 ? it - a.item0 : it;
-        const int stripe = pk.stripe;
+        const int stripe = a.stripe;
         const int per_stripe = stripe * a.items_y;
         const int st = local / per_stripe, loc = local - st * per_stripe;
         const int sw = min(stripe, a.items_x - st * stripe);
@@ -2425,10 +2425,9 @@ struct DpClass {
     bool blocks;  // scanned windows: the block kernel (or, for a launch, the scanning one)
     int rows = 0, cols = 0;  // and in a launch of one image its tile (not part of the class)
     int steps;    // most DP steps per launch allowed, 1..3 (tuning)
-    int stripe;   // item-order stripe of the multi-step kernels (tuning)
     bool operator==(const DpClass& o) const {
         return kind == o.kind && bound == o.bound && dc == o.dc && a16 == o.a16 &&
-               narrow == o.narrow && blocks == o.blocks && steps == o.steps && stripe == o.stripe;
+               narrow == o.narrow && blocks == o.blocks && steps == o.steps;
     }
 };
 
@@ -2540,7 +2539,6 @@ DpClass class_of(const DpJobSpec& j) {
     c.a16 = j.plan.a16;
     c.narrow = j.tables.narrow > 0;
     c.steps = j.plan.steps;
-    c.stripe = j.plan.stripe;
     c.blocks = false;
     if (j.plan.kind == WindowKind::Full && colmax_apply(j)) {
         c.kind = (int)WindowKind::Full;  // the column recurrence
@@ -2896,10 +2894,10 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
         a.w = g.w;
         a.items_x = (g.w + 63) / 64;
         a.items_y = (g.D + pair_rows - 1) / pair_rows;
+        a.stripe = std::max(1, J.plan.stripe);
     };
     auto launch_pairs = [&](DpPairPack<CAP>& pk, int cnt, long long total) {
         pk.count = cnt;
-        pk.stripe = std::max(1, c.stripe);
         bool pinned = false;
         size_t bytes = 0;  // two tables and V_{i+2} read, V_i and the links written
         for (int q = 0; q < cnt; ++q) {
@@ -2977,13 +2975,13 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
                 a.w = g.w;
                 a.items_x = (g.w + 63) / 64;
                 a.items_y = (g.D + kPairRows - 1) / kPairRows;
+                a.stripe = std::max(1, J->plan.stripe);
                 a.item0 = (int)total;
                 total += (long long)a.items_x * a.items_y;
                 if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
                 pk.job[cnt++] = a;
             }
             pk.count = cnt;
-            pk.stripe = std::max(1, c.stripe);
             e = launch_triple<AT, CAP>(jobs[0]->plan.bound, c.narrow, s, (int)total, pk);
         }
         if (e != hipSuccess) return e;

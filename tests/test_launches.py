@@ -134,3 +134,17 @@ def test_columns_of_the_recurrence(tmp, w, count, cols):
     got = launches.record(f"results = {call}", tmp)
     grids = [grid for m, grid, _ in got if launches.name(m) == "dp_colmax"]
     assert grids == [count * -(-w // cols)] * 2
+
+
+# Images of different widths, whose stripes of the pair kernel's order differ: the
+# stripe is each image's own, and they share their launches.
+@pytest.mark.parametrize("steps,kernel,count", [(2, "dp_pair_fixed", 3), (3, "dp_triple_fixed", 2)])
+def test_widths_of_a_batch_share_their_launches(tmp, steps, kernel, count):
+    shapes = [(512, w, 8, 1) for w in (700, 8200, 9500, 11000, 12500, 16000)]
+    got = launches.record(f"""
+from paper_1912_01884_amd import autotune
+fhtp.tune_set([autotune.rule(window=0, steps={steps}, stripe=4, w_max=1000),
+               autotune.rule(window=0, steps={steps})])
+results = batch({shapes}, [fhtp.make_bend(4)] * {len(shapes)})
+""", tmp)
+    assert [launches.name(m) for m, _, _ in got].count(kernel) == count
