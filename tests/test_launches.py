@@ -148,3 +148,15 @@ fhtp.tune_set([autotune.rule(window=0, steps={steps}, stripe=4, w_max=1000),
 results = batch({shapes}, [fhtp.make_bend(4)] * {len(shapes)})
 """, tmp)
     assert [launches.name(m) for m, _, _ in got].count(kernel) == count
+
+
+# 8-bit bands: both directions in a workgroup above 384 workgroups of them.
+@pytest.mark.parametrize("n,groups", [(32, 1), (64, 1), (128, 2)])
+def test_directions_of_the_transform(tmp, n, groups):
+    got = launches.record(f"""
+for k in (384 // {groups}, 384 // {groups} + 1):
+    fhtp._check(fhtp.lib().fhtp_fht_bands(PTR, 0, {n} * k, 60, k, PTR, PTR, 0, None), "fht_bands")
+    results += take()
+""", tmp)
+    assert [m.split("fht_split_kernelI")[1].split("E")[1] for m, _, _ in got] == ["Lb0", "Lb1"]
+    assert [grid for _, grid, _ in got] == [384 * 2, 384 + groups]
