@@ -328,7 +328,7 @@ def kernel_alg_bytes(family, model, launches):
         return model["fht_kernel"]  # the image read, every band's table written
     per_band = model["dp_per_band"]  # a band's table read, its back-pointers written
     bands = {"dp_pair_fixed": 2, "dp_triple_fixed": 3, "dp_step_fixed": 1,
-             "dp_step_blocks": 1}.get(family)
+             "dp_step_blocks": 1, "dp_step_generic": 1}.get(family)
     return None if bands is None else bands * per_band
 
 

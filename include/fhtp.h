@@ -305,7 +305,8 @@ int fhtp_plan_destroy(fhtp_plan plan);
  * bounds, the angle form and the unbounded bend; -1: any).  For the requests
  * it covers it sets:
  *   dc:       displacements per thread of one-step fixed-window launches, 8 or
- *             16 (0: the library's choice by grid size);
+ *             16 (0: the library's choice: 8 for images of at least four bands,
+ *             with fewer by grid size);
  *   steps:    the most DP steps one launch takes, 1, 2 or 3 (0: the
  *             library's choice, 2); two and three need dc 8 (or 0), three a
  *             bound of at most 8 shifts and no through-point pin (else two);
@@ -356,9 +357,9 @@ int fhtp_tune_get(fhtp_tune_rule* out, int cap, int* count);
  *   launches and the gaps between them, plus a little time of its own.
  * fhtp_timing_stop: turns timing off, waits for every recorded event, and
  *   returns one entry per kernel family in order of first launch: the family
- *   name ("fht_reg_kernel" (the FHT's one-pass kernels), "fht_combine_kernel", "dp_pair_fixed",
- *   "dp_step_fixed", "dp_step_blocks", "argmax_table", "walk",
- *   "prep_kernel", ...), its launch count and the summed
+ *   name ("fht_reg_kernel" (the FHT's one-pass kernels), "fht_combine_kernel",
+ *   "dp_pair_fixed", "dp_step_fixed", "dp_step_blocks", "dp_step_generic" (the
+ *   scanning kernel), "angle_windows", "argmax_table", "walk", "prep_kernel", ...), its launch count and the summed
  *   elapsed time of its brackets in milliseconds.  Up to `cap` entries
  *   are written to `out` (host memory); *count receives the number of
  *   families.  FHTP_ERR_HIP if an event could not be read (the entries are

@@ -3,8 +3,8 @@
 The library cuts its work into launches and workgroups by rules that never
 change a result (fhtp_tune_set, include/fhtp.h): the displacements per thread
 of one-step DP launches, how many DP steps (one, two or three) share a
-launch, the stripe width of the multi-step kernels' workgroup order, and whether the FHT runs a
-resident grid or one workgroup per work item.  ``tune`` times the candidates
+launch, the stripe width of the multi-step kernels' workgroup order, and whether the FHT of short
+bands runs a resident grid or one workgroup per work item.  ``tune`` times the candidates
 on the caller's own images through the batched entry point (the shapes a
 workload really launches, packed as they really are), checks that every
 candidate returns exactly the results of the library's defaults, and keeps
@@ -13,7 +13,8 @@ the fastest:
   1. the DP knobs, one choice for every fixed-window request of the workload
      (a shared choice keeps images of one window class in shared launches);
   2. then the FHT grid, separately for each (pixel type, band height) group
-     (FHT launches are grouped that way anyway).
+     (FHT launches are grouped that way anyway; for bands above 16 rows of 8-bit and
+     32 of 16-bit pixels both candidates are the same launches).
 
 The result is a list of rules, one pair per group plus a catch-all, that can
 be installed (``install``), saved as JSON keyed by the device name, its

@@ -67,7 +67,9 @@ constexpr int kXcds = 8;       // accelerator dies of the MI355X, each with its 
 // (SC1), written through the XCD's L2.  The next launch reads the planes from
 // every XCD; written through, they reach memory while the kernel runs instead
 // of in the L2 write-back at its end, which sits on the critical path of the
-// chain of step launches (about 1.2 us per launch at 4096 x 255 cells).
+// chain of step launches (about 1.2 us per launch at 4096 x 255 cells).  Of the
+// fixed-window and scanning kernels; the block kernel and the column recurrence
+// leave their planes to the L2s.
 constexpr int kStoreScope = 16;
 // Pair launches that move more than this leave V_i to the L2s (32 MB in all, which
 // such a launch turns over anyway; then a written-through plane only waits for

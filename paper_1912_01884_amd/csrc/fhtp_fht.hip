@@ -185,7 +185,6 @@ struct FhtJob {
     int item0;        // first work item of this run in the launch
     int to_table;     // 1: band tables; 0: c-space sub-block scratch
     int narrow;       // bands stored as uint16 (the rest, from band `narrow` on, go to out)
-    int sub16;        // scratch as uint16 (8-bit pixels: a 128-row sum is at most 32640)
 };
 
 constexpr int kPack = 256;  // runs per launch (kernel arguments of up to 32 KB)
@@ -385,7 +384,7 @@ __global__ __launch_bounds__(RegCfg<P>::NT) void fht_reg_kernel(FhtPack<CAP> pk)
         if constexpr (sizeof(PixT) == 1 && P >= 2) {
             // Stages 1 .. p-1 never mix the top and bottom halves of the
             // block, and apply the same shifts to both.  With 8-bit pixels a
-            // half's sums stay below 2^16 (at most 64 * 255), so row y and row
+            // half's sums stay below 2^16 (at most 8 * 255), so row y and row
             // y + n/2 share a register (low and high 16 bits, no carry between
             // them) and those stages run as the recursion of a block of n/2
             // rows on n/2 registers: half the LDS exchange and half the adds.
@@ -461,6 +460,10 @@ struct SplitCfg {
     static constexpr int R = 1 << Q;               // rows in a base sum
     static constexpr int G = 1 << Q;               // groups of shifts
     static constexpr int M = 8;                    // blocks
+    // 512 threads for 256-row bands, for the int32 tables of large 8-bit images: us of the
+    // band tables of 8192 x 16384 476, with 1024 threads 532 (4096 x 16384 242 / 267).
+    // Elsewhere 1024 would be the faster: in detections of 4096 x 4096 61.3 / 56.4 of 8-bit
+    // and 74.9 / 71.0 of 16-bit pixels, of 8192 x 16384 406 / 395 and 531 / 535.
     static constexpr int NT = P <= 7 ? 1024 : 512;
     static constexpr int ROWS = NF * R;            // rows of a block
     static constexpr int WC = 57;                  // columns a wave of phase 1 makes
@@ -507,7 +510,7 @@ __device__ __forceinline__ void lane_stage(int32_t (&v)[ROWS][COLS]) {
 #pragma unroll
             for (int h = 0; h < COLS; ++h) v[b * 2 * half + q][h] = o[q][h];
     }
-    // final here, as in fht_stage_free
+    // final here, as in fht_stages
 #pragma unroll
     for (int q = 0; q < ROWS; ++q)
 #pragma unroll
@@ -943,7 +946,6 @@ struct RegRun {
     uint16_t* out16;
     int narrow;
     int grid_mode;  // 0: resident grid; 1: one workgroup per item
-    int sub16;
 };
 
 template <int P, typename PixT, int CAP>
@@ -981,7 +983,6 @@ hipError_t launch_reg_pack(const RegRun* runs, int count, hipStream_t stream) {
         J.to_table = r.to_table;
         J.out16 = r.out16;
         J.narrow = r.narrow;
-        J.sub16 = r.sub16;
         total += (long long)tiles * r.blocks * C::NDIR;
         if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     }
@@ -1019,7 +1020,6 @@ hipError_t launch_split_as(const RegRun* runs, int count, hipStream_t stream) {
         J.to_table = r.to_table;
         J.out16 = r.out16;
         J.narrow = r.narrow;
-        J.sub16 = r.sub16;
         total += (long long)tiles * r.blocks * C::G * (BOTH ? 1 : 2);
         if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     }
@@ -1130,7 +1130,6 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
         r.out16 = J.tables.narrow ? J.tables.tab16 : nullptr;
         r.narrow = 0;
         r.grid_mode = J.grid_mode;
-        r.sub16 = 0;
         if (g.p <= kOnePassMax) {
             r.p = g.p;
             r.blocks = g.k;
@@ -1142,7 +1141,6 @@ hipError_t launch_fht_jobs(const FhtJobSpec* jobs, int count, hipStream_t stream
             r.blocks = g.h >> kRegMaxP;
             r.to_table = 0;
             r.out = static_cast<int32_t*>(J.scratch);
-            r.sub16 = J.dtype == 0;
         }
         // Only the register kernel's grid has a choice: elsewhere it must not keep
         // runs from sharing a launch.

@@ -54,7 +54,7 @@ private:
     hipEvent_t begin_ = nullptr;
 };
 
-// Row blocks (log2) that bands transformed in two passes are cut into.
+// Row blocks (log2) that bands transformed in two passes (above 256 rows) are cut into.
 constexpr int kRegMaxP = 7;
 
 // ---- band tables ------------------------------------------------------------
@@ -75,7 +75,7 @@ inline bool narrow_tables_apply(const Geometry& g, int dtype) {
 }
 
 // ---- band FHT -------------------------------------------------------------
-// Scratch needed by launch_fht (bytes, 0 when n <= 2^kRegMaxP); dtype 0 =
+// Scratch a caller gives launch_fht (bytes, 0 when n <= 2^kRegMaxP; used above 256 rows); dtype 0 =
 // uint8 pixels (16-bit scratch cells), 1 = uint16 pixels (32-bit cells).
 size_t fht_scratch_bytes(const Geometry& g, int dtype);
 
