@@ -1481,220 +1481,37 @@ struct BlkLds {
 
 // Column tile `local` of image a.
 template <int ROWS, int COLS, typename AT, typename TT>
-__device__ __forceinline__ void blocks_tile(const DpJob& a, int local, BlkLds<ROWS, COLS>& m_) {
-    using C = BlkCfg<ROWS, COLS>;
-    constexpr int NB = C::NB, LV = C::levels();
-    auto& vt = m_.vt;
-    auto& pre_v = m_.pre_v;
-    auto& suf_v = m_.suf_v;
-    auto& ps_i = m_.ps_i;
-    auto& run_v = m_.run_v;
-    auto& run_i = m_.run_i;
-    auto& wlo = m_.wlo;
-    auto& whi = m_.whi;
-    auto at = [](int r, int c) { return r * COLS + c + (r / kBlk) * COLS; };
-    const int n = a.n, w = a.w, D = 2 * n - 1;
-    const int t = threadIdx.x;
-    const int c = t % COLS;
-    const int rq = t / COLS;  // first row of the thread's cells rq, rq + LANES, ...
-    const int xp = local * COLS + c;
-
-    // A tile whose every cell, window row and successor lies inside the image
-    // (and carries no pin) takes its addresses from one lane offset per plane.
-    const int X0 = local * COLS;
-    const bool inner = D == ROWS - 1 && a.vin_pin == 0 && X0 - (n - 1) >= 0 &&
-                       X0 + COLS - 1 + (n - 1) < w &&
-                       (unsigned long long)D * (unsigned)max(a.h_pitch, a.vin_pitch) < (1u << 30);
-    // H_i(x' - d, d) of the thread's cells, in flight during the scans
-    int hv[C::OUT];
-    if (inner) {
-        const TT* h = static_cast<const TT*>(a.htab);
-        const unsigned int o = (unsigned int)(rq * (a.h_pitch - 1) + xp + n - 1);
-#pragma unroll
-        for (int j = 0; j < C::OUT; ++j) {
-            // (the table's rows end at D - 1: the tile's last row reads the one above)
-            const bool pad = j == C::OUT - 1 && rq + C::LANES * j >= D;
-            hv[j] = (int)(h + (ptrdiff_t)(C::LANES * j) * (a.h_pitch - 1))[pad ? o - a.h_pitch : o];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < C::OUT; ++j) hv[j] = load_h<TT>(a, xp, rq + C::LANES * j - (n - 1));
-    }
-    if (rq < NB) {
-        // block rq of column c: prefix maxima ascending (ties keep the first),
-        // suffix maxima descending (ties move to the smaller row)
-        const int r0 = rq * kBlk;
-        int v[kBlk];
-        if (inner) {
-            const unsigned int o = (unsigned int)(r0 * a.vin_pitch + xp);
-#pragma unroll
-            for (int q = 0; q < kBlk; ++q) {
-                const bool pad = q == kBlk - 1 && r0 + q >= D;
-                const int u = (a.vin + (ptrdiff_t)q * a.vin_pitch)[pad ? o - a.vin_pitch : o];
-                v[q] = pad ? -1 : u;
-            }
-        } else {
-            const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
-#pragma unroll
-            for (int q = 0; q < kBlk; ++q)
-                v[q] = load_v(a.vin, a.vin_pitch, xp, r0 + q - (n - 1), n, mk);  // -1 past row D-1
-        }
-        int sv[kBlk], si[kBlk];
-        sv[kBlk - 1] = v[kBlk - 1];
-        si[kBlk - 1] = kBlk - 1;
-#pragma unroll
-        for (int q = kBlk - 2; q >= 0; --q) {
-            const bool take = v[q] >= sv[q + 1];
-            sv[q] = take ? v[q] : sv[q + 1];
-            si[q] = take ? q : si[q + 1];
-        }
-        int pv = v[0], pi = 0;
-#pragma unroll
-        for (int q = 0; q < kBlk; ++q) {
-            const bool take = v[q] > pv;
-            pv = take ? v[q] : pv;
-            pi = take ? q : pi;
-            const int o = at(r0, c) + q * COLS;
-            vt[o] = v[q];
-            pre_v[o] = pv;
-            suf_v[o] = sv[q];
-            ps_i[(r0 + q) * COLS + c] = (unsigned char)(pi | (si[q] << 4));
-        }
-        run_v[0][rq][c] = sv[0];
-        run_i[0][rq][c] = (unsigned short)(r0 + si[0]);
-    }
-    for (int r = t; r < D; r += C::THREADS) {
-        int lo, hi;
-        if (a.make_win) {
-            // the first step makes the angle form's windows for itself, and one
-            // of its workgroups leaves them to later launches
-            angle_window(n, a.tan_gamma, r - (n - 1), lo, hi);
-            if (local == 0) {
-                a.win[r] = lo;
-                a.win[D + r] = hi;
-            }
-        } else {
-            window_of(n, a.full, a.win, a.bound, r - (n - 1), lo, hi);
-        }
-        wlo[r] = (unsigned short)(lo + n - 1);
-        whi[r] = (unsigned short)(hi + n - 1);
-    }
-    __syncthreads();
-    if (rq < NB) {
-        // runs of 2, 4, .. blocks from block rq, ascending (ties keep the first)
-        int mv = run_v[0][rq][c], mi = run_i[0][rq][c];
-#pragma unroll
-        for (int l = 1; l < LV; ++l) {
-#pragma unroll 8
-            for (int b = (1 << (l - 1)); b < (1 << l); ++b) {
-                const int bb = min(rq + b, NB - 1);
-                const int v = run_v[0][bb][c];
-                const int vi = run_i[0][bb][c];
-                const bool take = rq + b < NB && v > mv;
-                mv = take ? v : mv;
-                mi = take ? vi : mi;
-            }
-            run_v[l][rq][c] = mv;
-            run_i[l][rq][c] = (unsigned short)mi;
-        }
-    }
-    __syncthreads();
-
-    const bool last = a.key != nullptr;  // the image's last step: keys, no planes
-    const bool col = xp < w;
-    Best best;
-#pragma unroll
-    for (int j = 0; j < C::OUT; ++j) {
-        const int r = rq + C::LANES * j;
-        if (r >= D) break;
-        const int lo = wlo[r], hi = whi[r];
-        const int bl = lo / kBlk, bh = hi / kBlk;
-        int m, ia;
-        if (bl == bh) {
-            // straight-line groups of four reads at constant offsets (what lies past
-            // the window is read, not used)
-            const int* cells = &vt[at(lo, c)];
-            const int len = hi - lo;
-            m = cells[0];
-            int im = 0;
-#pragma unroll
-            for (int q0 = 1; q0 < kBlk; q0 += 4) {
-                if (q0 > len) break;
-                int v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (q0 + u < kBlk) v[u] = cells[(q0 + u) * COLS];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (q0 + u >= kBlk) break;
-                    const bool take = v[u] > m && q0 + u <= len;
-                    m = take ? v[u] : m;
-                    im = take ? q0 + u : im;
-                }
-            }
-            ia = lo + im;
-        } else {
-            m = suf_v[at(lo, c)];
-            ia = bl * kBlk + (ps_i[lo * COLS + c] >> 4);
-            const int cnt = bh - bl - 1;  // whole blocks between
-            if (cnt > 0) {
-                const int l = 31 - __builtin_clz((unsigned)cnt);
-                const int v1 = run_v[l][bl + 1][c], v2 = run_v[l][bh - (1 << l)][c];
-                const int i1 = run_i[l][bl + 1][c], i2 = run_i[l][bh - (1 << l)][c];
-                const bool t1 = v1 > m;
-                m = t1 ? v1 : m;
-                ia = t1 ? i1 : ia;
-                const bool t2 = v2 > m;
-                m = t2 ? v2 : m;
-                ia = t2 ? i2 : ia;
-            }
-            const int vp = pre_v[at(hi, c)];
-            const bool tp = vp > m;
-            m = tp ? vp : m;
-            ia = tp ? bh * kBlk + (ps_i[hi * COLS + c] & 15) : ia;
-        }
-        if (!col) continue;
-        const int x = xp - (r - (n - 1));
-        const int val = m >= 0 && (a.out_pin_x < 0 || x == a.out_pin_x) ? hv[j] + m : -1;
-        if (last) {
-            if ((unsigned)x < (unsigned)w) take_best(best, pack_key(val, x, r, D), ia);
-            continue;
-        }
-        (static_cast<AT*>(a.aout) + (size_t)r * a.pitch)[xp] = (AT)ia;
-        if ((unsigned)x < (unsigned)w) (a.vout + (size_t)r * a.pitch)[x] = val;
-    }
-    if (last) {
-        // the workgroup's best key and that cell's successor, slot = column tile
-        constexpr int W = BlkLds<ROWS, COLS>::WAVES;
-        auto& part = m_.part;
-        auto& part_s = m_.part_s;
-        const int lane = t & 63, wave = t >> 6;
-        best = wave_best(best);
-        if (lane == 0) {
-            part[wave] = best.key;
-            part_s[wave] = best.succ;
-        }
-        __syncthreads();
-        if (t == 0) {
-            unsigned long long mk2 = part[0];
-            int ms = part_s[0];
-#pragma unroll
-            for (int q = 1; q < W; ++q) {
-                const bool tk = part[q] > mk2;
-                mk2 = tk ? part[q] : mk2;
-                ms = tk ? part_s[q] : ms;
-            }
-            a.key[local] = mk2;
-            a.succ[local] = ms;
-        }
-    }
+__device__ __forceinline__ void blocks_tile(const DpJob& a, int local, BlkLds<ROWS, COLS>& lds) {
+    auto& vt = lds.vt;
+    auto& pre_v = lds.pre_v;
+    auto& suf_v = lds.suf_v;
+    auto& ps_i = lds.ps_i;
+    auto& run_v = lds.run_v;
+    auto& run_i = lds.run_i;
+    auto& wlo = lds.wlo;
+    auto& whi = lds.whi;
+    auto& part = lds.part;
+    auto& part_s = lds.part_s;
+#include "fhtp_blocks_tile.inc"
 }
 
 // One image a launch: tiles as wide as the chip needs (blk_cols).
 template <int ROWS, int COLS, typename AT, typename TT>
 __global__ __launch_bounds__((BlkCfg<ROWS, COLS>::THREADS)) void dp_step_blocks(DpPack<1> pk) {
-    __shared__ BlkLds<ROWS, COLS> lds;
-    blocks_tile<ROWS, COLS, AT, TT>(pk.job[0], xcd_run_item((int)blockIdx.x, (int)gridDim.x), lds);
+    using L = BlkLds<ROWS, COLS>;
+    __shared__ decltype(L::vt) vt;
+    __shared__ decltype(L::pre_v) pre_v;
+    __shared__ decltype(L::suf_v) suf_v;
+    __shared__ decltype(L::ps_i) ps_i;
+    __shared__ decltype(L::run_v) run_v;
+    __shared__ decltype(L::run_i) run_i;
+    __shared__ decltype(L::wlo) wlo;
+    __shared__ decltype(L::whi) whi;
+    __shared__ decltype(L::part) part;
+    __shared__ decltype(L::part_s) part_s;
+    const DpJob& a = pk.job[0];
+    const int local = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
+#include "fhtp_blocks_tile.inc"
 }
 
 // Tile of the block kernel: the rows it holds (D < rows), and its most columns (what
