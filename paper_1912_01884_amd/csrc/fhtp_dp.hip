@@ -2092,18 +2092,24 @@ __global__ __launch_bounds__(64 * kColWaves) void dp_colmax(ColPack<CAP> pk) {
     }
     __syncthreads();
     if (wave != 0) return;
-    if (lane < COLS) {
-        // waves hold ascending row ranges: a later wave wins only when larger
+    // waves hold ascending row ranges: a later wave wins only when larger (every read
+    // first: a choice's row read where it is chosen waits for each in turn)
+    int wv[kColWaves], wr[kColWaves];
 #pragma unroll
-        for (int q = 1; q < kColWaves; ++q) {
-            const bool t = pv[q][c] > best;
-            best = t ? pv[q][c] : best;
-            brow = t ? pr[q][c] : brow;
-        }
-        if (col) {
-            static_cast<AT*>(a.bout)[x] = (AT)brow;
-            if (a.uout) a.uout[x] = best;
-        }
+    for (int q = 1; q < kColWaves; ++q) {
+        wv[q] = pv[q][c];
+        wr[q] = pr[q][c];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 1; q < kColWaves; ++q) {
+        const bool t = wv[q] > best;
+        best = t ? wv[q] : best;
+        brow = t ? wr[q] : brow;
+    }
+    if (lane < COLS && col) {
+        static_cast<AT*>(a.bout)[x] = (AT)brow;
+        if (a.uout) a.uout[x] = best;
     }
     if (a.key) {
         const unsigned long long kk = wave_max_u64(lane < COLS && col ? col_key(best, x) : 0ull);
