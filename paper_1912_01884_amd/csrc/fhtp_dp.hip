@@ -95,8 +95,7 @@ struct DpJob {
         };
         double tan_gamma;  // of a step that makes the mode-1 windows
     };
-    int vin_pitch, h_pitch;
-    int pitch;    // of V_i and A_{i+1}
+    int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w;
     int make_win; // the image's first step makes win
     int items_x;  // workgroups along x
@@ -392,7 +391,7 @@ __device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const Ro
     if (xp >= w || r >= D) return;
     const bool last = a.key != nullptr;
     if (!last) {
-        const unsigned int arow = row_off(av, r, a.pitch, sizeof(AT));
+        const unsigned int arow = row_off(av, r, a.a_pitch, sizeof(AT));
         const unsigned int aval = (unsigned int)(ra < 0 ? 0 : ra);
         if constexpr (sizeof(AT) == 1)
             __builtin_amdgcn_raw_buffer_store_b8((unsigned char)aval, av.rs, xp, (int)arow,
@@ -407,7 +406,7 @@ __device__ __forceinline__ void emit(const DpJob& a, const RowView& ov, const Ro
     if (last) {
         take_best(best, pack_key(val, x, r, D), ra);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.pitch, 4),
+        __builtin_amdgcn_raw_buffer_store_b32(val, ov.rs, x * 4, (int)row_off(ov, r, a.v_pitch, 4),
                                               kStoreScope);
     }
 }
@@ -567,14 +566,14 @@ __device__ __forceinline__ Best fixed_interior(const DpJob& a, int X0, int r0, i
         }
         return best;
     }
-    const unsigned int op = (unsigned int)a.pitch * 4u;
-    const unsigned int ap = (unsigned int)a.pitch * sizeof(AT);
+    const unsigned int op = (unsigned int)a.v_pitch * 4u;
+    const unsigned int ap = (unsigned int)a.a_pitch * sizeof(AT);
     // the V_i cells lie on the same diagonal as the table cells, at 4 bytes a cell
     const unsigned int vdiag = (unsigned int)(xp - d0 - (DC - 1)) * 4u;
     const __amdgpu_buffer_rsrc_t orr = __builtin_amdgcn_make_buffer_rsrc(
-        a.vout + (size_t)r0 * a.pitch, (short)0, (int)(DC * op), 0x00020000);
+        a.vout + (size_t)r0 * a.v_pitch, (short)0, (int)(DC * op), 0x00020000);
     const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(
-        static_cast<AT*>(a.aout) + (size_t)r0 * a.pitch, (short)0, (int)(DC * ap), 0x00020000);
+        static_cast<AT*>(a.aout) + (size_t)r0 * a.a_pitch, (short)0, (int)(DC * ap), 0x00020000);
 #pragma unroll
     for (int j = 0; j < DC; ++j) {
         const int val = m[j] >= 0 ? hv[j] + m[j] : -1;
@@ -652,10 +651,10 @@ __device__ __forceinline__ Best fixed_general(const DpJob& a, int X0, int r0, in
         }
         return best;
     }
-    const RowView aview = row_view(a.aout, a.pitch, esz, r0, DC, D);
-    const RowView oview = row_view(a.vout, a.pitch, 4, r0, DC, D);
-    const unsigned int ap = (unsigned int)a.pitch * (unsigned int)esz;
-    const unsigned int op = (unsigned int)a.pitch * 4u;
+    const RowView aview = row_view(a.aout, a.a_pitch, esz, r0, DC, D);
+    const RowView oview = row_view(a.vout, a.v_pitch, 4, r0, DC, D);
+    const unsigned int ap = (unsigned int)a.a_pitch * (unsigned int)esz;
+    const unsigned int op = (unsigned int)a.v_pitch * 4u;
     const unsigned int ab = (unsigned int)(r0 - aview.base) * ap + (unsigned int)xp * (unsigned int)esz;
     const unsigned int ob = (unsigned int)(r0 - oview.base) * op + (unsigned int)xj * 4u;
 #pragma unroll
@@ -758,7 +757,7 @@ struct DpPairJob {
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w, items_x, items_y;
     int item0;   // first workgroup of this image in the launch
-    int stripe;  // column tiles per stripe of the item order
+    int stripe;  // column tiles per stripe of the item order (in packs of images)
     // Through-point pin: on the cells read from vin (the table H_{k-1} read as
     // V_{k-1}: 0 none, 1 x'' == pin, 2 x'' + d'' == pin), and on the cells of
     // V_{i+1} (pin1_x) and V_i (pin0_x) made here (-1: none).
@@ -771,6 +770,7 @@ template <int CAP>
 struct DpPairPack {
     DpPairJob job[CAP];
     int count;
+    int stripe;   // of one image (read from its descriptor, the largest bounds spill registers)
     int through;  // write V_i through to memory (see kThroughBytes)
 };
 
@@ -799,7 +799,7 @@ __global__ __launch_bounds__((64 * PairShape<SMALL>::WAVES)) void dp_pair_fixed(
     __shared__ AT nxt[NS * STRIP][LWP];   // row of that cell's window maximum (its choice)
 
     // Workgroup b runs on XCD b % 8.  Each XCD gets a contiguous run of items
-    // instead, an image's items in stripes of a.stripe column tiles (every
+    // instead, an image's items in stripes of `stripe` column tiles (every
     // row group of a stripe before the next stripe), so that the overlapping
     // reads of neighbouring workgroups (the widened rows, a strip's extra
     // columns, the diagonal shift between row groups) meet in one L2.
@@ -821,7 +821,7 @@ __global__ __launch_bounds__((64 * PairShape<SMALL>::WAVES)) void dp_pair_fixed(
     int bx, by;
     {
         const int local = CAP > 1 ? it - a.item0 : it;  // one image: item0 is 0
-        const int stripe = a.stripe;
+        const int stripe = CAP > 1 ? a.stripe : pk.stripe;
         const int per_stripe = stripe * a.items_y;
         const int st = local / per_stripe, loc = local - st * per_stripe;
         const int sw = min(stripe, a.items_x - st * stripe);
@@ -998,13 +998,14 @@ struct DpTripleJob {
     int vin_pitch, h_pitch, v_pitch, a_pitch;
     int n, w, items_x, items_y;
     int item0;   // first workgroup of this image in the launch
-    int stripe;  // column tiles per stripe of the item order
+    int stripe;  // column tiles per stripe of the item order (in packs of images)
 };
 
 template <int CAP>
 struct DpTriplePack {
     DpTripleJob job[CAP];
     int count;
+    int stripe;  // as DpPairPack
 };
 
 template <int B, typename AT, int CAP, typename TT>
@@ -1032,7 +1033,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     __shared__ AT nx2[NS1 * kStrip][LWP];   // its choice's choice (a row of V_{i+3})
 
     // Item order as in dp_pair_fixed: contiguous runs per XCD, walked in
-    // stripes of a.stripe column tiles.
+    // stripes of `stripe` column tiles.
     const int it = xcd_run_item((int)blockIdx.x, (int)gridDim.x);
     int jj = 0;
     if constexpr (CAP > 1) {
@@ -1051,7 +1052,7 @@ __global__ __launch_bounds__(64 * kPairWaves) void dp_triple_fixed(DpTriplePack<
     int bx, by;
     {
         const int local = CAP > 1 ? it - a.item0 : it;
-        const int stripe = a.stripe;
+        const int stripe = CAP > 1 ? a.stripe : pk.stripe;
         const int per_stripe = stripe * a.items_y;
         const int st = local / per_stripe, loc = local - st * per_stripe;
         const int sw = min(stripe, a.items_x - st * stripe);
@@ -1292,8 +1293,8 @@ __global__ __launch_bounds__(64 * kWaves) void dp_step_generic(DpPack<CAP> pk) {
     const int jn = min(kDCGeneric, D - (d0 + n - 1));  // displacements of this wave
     const DRange mk = drange(n, xp, vmask(w, a.vin_pin, a.vin_pin_x));
     const bool last = a.key != nullptr;  // no planes to write (views unused)
-    const RowView ov = row_view(last ? a.vin : a.vout, a.pitch, 4, d0 + n - 1, kDCGeneric, D);
-    const RowView av = row_view(last ? a.vin : a.aout, a.pitch, sizeof(AT), d0 + n - 1,
+    const RowView ov = row_view(last ? a.vin : a.vout, a.v_pitch, 4, d0 + n - 1, kDCGeneric, D);
+    const RowView av = row_view(last ? a.vin : a.aout, a.a_pitch, sizeof(AT), d0 + n - 1,
                                 kDCGeneric, D);
     int hv[kDCGeneric];
 #pragma unroll
@@ -2483,7 +2484,8 @@ DpJob base_job(const DpJobSpec& J) {
     a.full = J.plan.kind == WindowKind::Full;
     a.win = J.plan.kind == WindowKind::Angle ? J.buf.win : nullptr;
     a.h_pitch = g.W;
-    a.pitch = g.pitch;
+    a.v_pitch = g.pitch;
+    a.a_pitch = g.pitch;
     a.items_x = (g.w + 63) / 64;
     a.out_pin_x = -1;
     return a;
@@ -2723,6 +2725,7 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
     };
     auto launch_pairs = [&](DpPairPack<CAP>& pk, int cnt, long long total) {
         pk.count = cnt;
+        pk.stripe = pk.job[0].stripe;
         bool pinned = false;
         size_t bytes = 0;  // two tables and V_{i+2} read, V_i and the links written
         for (int q = 0; q < cnt; ++q) {
@@ -2807,6 +2810,7 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
                 pk.job[cnt++] = a;
             }
             pk.count = cnt;
+            pk.stripe = pk.job[0].stripe;
             e = launch_triple<AT, CAP>(jobs[0]->plan.bound, c.narrow, s, (int)total, pk);
         }
         if (e != hipSuccess) return e;
