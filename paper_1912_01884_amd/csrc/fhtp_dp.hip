@@ -687,10 +687,18 @@ __device__ __forceinline__ Best fixed_item(const DpJob& a, int bx, int by) {
     return fixed_general<B, DC, AT, TT>(a, X0, r0, d0);
 }
 
+// Most waves per SIMD the fixed-window step is compiled for: what its registers allow
+// with every load of a thread in flight.  Given the choice, the compiler holds loads
+// back at the bounds that just miss one wave more: 1024 x 1024, k = 16, bound 12, one
+// step a launch 142 us a detection against 75.
+template <int B, int DC>
+constexpr int kStepWaves = DC == 8 ? (B >= 11 ? 7 : 8) : (B >= 15 ? 4 : 8);
+
 // Step with the mode-0 window fixed at compile time.  TT: the table's
 // element type (int32, or uint16 for narrow tables).
 template <int B, int DC, typename AT, int CAP, typename TT>
-__global__ __launch_bounds__(64 * kWaves) void dp_step_fixed(DpPack<CAP> pk) {
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, kStepWaves<B, DC>)))
+void dp_step_fixed(DpPack<CAP> pk) {
     // items of an image run down the displacement groups of one column tile
     // before the next tile, so the window rows shared by vertical neighbours
     // meet in one L2
