@@ -46,7 +46,7 @@
 // different sizes shares one launch per step (or pair of steps) instead of one
 // per image and step.  One step per launch: an image with k bands takes part
 // in the launches s = 0 .. k-2 of its pack (band i = k-2-s).  Two steps per
-// launch: images are aligned at their last step (run_steps_paired).
+// launch: images are aligned at their last step (run_steps_grouped).
 #include <algorithm>
 #include <memory>
 #include <type_traits>
@@ -1275,7 +1275,7 @@ __device__ __forceinline__ void angle_window(int n, double t, int d, int& lo, in
 // [lo, c] maximum (recorded as the scan passes each lo) and one ascending scan
 // from c+1 gives every [c+1, hi] maximum, so each V cell of the union of the
 // windows is read and compared once, with the loads issued eight at a time.  Its
-// time is the windows' length (about 0.05 ps a cell and row beside 3.5 ps a cell at
+// time is the windows' length (about 0.05 ps a cell and row beside 3.2 ps a cell at
 // 2048 x 16384 and above), in rows of 64 columns where the block kernel's tiles of
 // tall bands have 4 to 16.
 // Ties keep the smallest d' (descending scans take equal values, ascending
@@ -1997,9 +1997,9 @@ __global__ __launch_bounds__(64) void angle_windows(int n, double t, int32_t* __
 // threads take a column and a run of rows each, ascending, and their partial
 // maxima meet first in the wave, then in LDS (larger values win, the smaller row
 // where equal).  Bound by the chain of a launch (its loads are one round trip
-// where a thread has at most 8 rows): 3.6 us at 1501 columns of 255 displacements,
-// 4.5 with 64 columns a workgroup, of which a chip then has 24.  Rows dealt out
-// one by one instead of in runs: 82.0 against 73.6 us a detection.
+// where a thread has at most 8 rows): 3.3 us at 1501 columns of 255 displacements.
+// Rows dealt out one by one instead of in runs: 82.0 against 73.6 us a detection; the
+// partial maxima's rows read only where they are chosen 72.3 against 66.8.
 constexpr int kColWaves = 16;
 
 struct ColJob {
@@ -2312,6 +2312,30 @@ double mean_window(const DpJobSpec& J) {
     return rows < D ? rows : D;
 }
 
+// The fewest columns from which an image of bands of 2 to 32 rows, alone in its
+// launches, takes the scanning kernel.  The block kernel's shortest tile is mostly
+// padding there, which tells once the image has several workgroups a CU (a round of
+// them is 8192 columns); a scan takes longest where every window is a group of its own
+// or is long, and without a limit, where it serves all rows of a column at once, hardly
+// any time.  The block kernel's time over the scan's (steps and walk, k = 8):
+//   3 displacements            w = 8192 0.76, 12288 1.07, 16384 1.15, 40960 2.2
+//   7 to 31, windows of 1 to 4 rows  16384 0.70-0.88, 24576 0.92-1.2, 40960 1.3-1.8
+//            5 to 10                 16384 0.93-1.05, 18432 1.03-1.3
+//            14                      14336 0.96, 16384 1.06-1.08
+//            31                      16384 0.82-0.89, 18432 0.95-1.05
+//   63,      3                       32768 0.98, 40960 1.03
+//            10                      16384 0.91, 18432 1.01
+//            27                      20480 0.95, 24576 1.08
+//            35, 63                  40960 0.98, 0.89
+//   no limit, with a pin (a detection): 3 to 15 displacements 8192 0.99-1.08, 31 8192
+//   0.97, 12288 1.3, 63 8192 0.90, 12288 1.1
+int scan_width(int n, bool full, double rows) {
+    if (full) return n <= 8 ? 8192 : 8193;
+    if (n == 2) return 12288;
+    if (n == 32) return rows < 5.0 ? 40960 : rows < 20.0 ? 16385 : rows < 30.0 ? 24576 : 49152;
+    return rows < 5.0 ? 24576 : rows > 10.0 && rows < 20.0 ? 16384 : 16385;
+}
+
 // Whether an image alone in its launches takes the scanning kernel: the block
 // kernel's time is its tiles', whatever the windows, and its tiles become narrower as
 // bands become taller; the scanning kernel's grows with the windows.  Measured (us
@@ -2322,19 +2346,11 @@ double mean_window(const DpJobSpec& J) {
 //                      8192 164 / 142, bound 25 (51) 163 / 162, 40 (81) 163 / 201
 //   2048:              w = 300 bound 17 40 / 35; 4096 204 / 144, bound 40 204 / 202;
 //                      16384 838 / 735, bound 100 833 / 1287
-// The block kernel's shortest tile is mostly padding on bands of few rows, which tells
-// once the image has several workgroups a CU (and without a limit, where a scan
-// serves all rows of a column at once): 7 displacements at w = 16384 50 / 69 and at
-// 40000 105 / 71, 31 at 16384 (0.02 rad) 57 / 78 and at 40000 118 / 91, 63 at 40000
-// 123 / 118; 3 with a pin at 16384 56 / 48; 15 without a limit, with a pin, a
-// detection at 4096 41.8 / 41.1, 8192 45.4 / 40.8, 40000 148 / 50.
 bool scan_alone(const DpJobSpec& J) {
     const Geometry& g = J.g;
     const double w = g.w, rows = mean_window(J);
     switch (blk_rows(g.D)) {
-        case 64:
-            if (J.plan.kind == WindowKind::Full) return g.w >= 8192;
-            return g.w >= (g.n == 2 ? 12288 : g.n == 32 ? 32768 : rows < 5.0 ? 24576 : 18432);
+        case 64: return g.w >= scan_width(g.n, J.plan.kind == WindowKind::Full, rows);
         case 512: return g.w >= 4096 && rows <= 40.0 * w / (w + 2900.0);
         case 1024: return rows <= 62.0 * w / (w + 2800.0);
         case 2048: return rows <= std::max(35.0, 100.0 * w / (w + 1300.0));
@@ -2853,11 +2869,11 @@ hipError_t run_steps_grouped(const DpClass& c, int G, const std::vector<const Dp
 // Columns of a workgroup of the column recurrence in launches of `columns` columns
 // in all: the fewest that need at most one workgroup per CU, 64 (a wave's row of
 // them) at most.  us without a bend limit: detections of 16-bit images at 8 / 16 / 32
-// / 64 columns, 2048 x 1501, k = 16 73.6 / 73.8 / 78.7 / 94.8, 4096 x 4096, k = 32
-// 194 / 180 / 185 / 220, 2048 x 8000, k = 16 146 / 106 / 101 / 118; steps and walk at
-// 32 / 64, k = 8, 1024 x 12000 45.6 / 43.2, 1024 x 32768 120 / 87, 512 x 24000 51 / 43.
+// / 64 columns, 2048 x 1501, k = 16 66.8 / 66.9 / 71.9 / 87.9, 4096 x 4096, k = 32
+// 186 / 168 / 176 / 207, 2048 x 8000, k = 16 153 / 121 / 114 / 127; steps and walk at
+// 32 / 64, k = 8, 1024 x 12000 42.0 / 40.0, 1024 x 32768 113 / 83, 512 x 24000 47 / 40.
 // A pack of images takes 32 or 64 by all of its columns (16 images 1024 x 2000, k = 16
-// 202 / 170).
+// 196 / 166).
 int col_cols(long long columns, bool alone) {
     constexpr int kCus = 256;
     int c = alone ? 8 : 32;

@@ -34,7 +34,7 @@ def _check(dev, img, k, pin=None, **bend):
 
 
 CASES = [(1, 1, 5), (1, 63, 5), (1, 64, 4), (1, 4097, 9), (2, 12288, 4), (8, 24577, 3),
-         (16, 18500, 3), (32, 32768, 3), (256, 4096, 3), (512, 300, 3), (512, 4097, 2),
+         (16, 18500, 3), (32, 32768, 3), (32, 40961, 2), (256, 4096, 3), (512, 300, 3), (512, 4097, 2),
          (1024, 65, 3), (1024, 300, 2)]
 
 

@@ -91,14 +91,24 @@ def test_heights_of_a_batch_share_their_step_launches(tmp, bend):
     (1, 3000, "fhtp.make_bend(5)", True, True),
     (2, 12287, "fhtp.make_bend(None, 0.3)", True, False),
     (2, 12288, "fhtp.make_bend(None, 0.3)", True, True),
-    (16, 18431, "fhtp.make_bend(None, 0.3)", False, False),
-    (16, 18432, "fhtp.make_bend(None, 0.3)", False, True),
+    (16, 16383, "fhtp.make_bend(None, 0.3)", False, False),
+    (16, 16384, "fhtp.make_bend(None, 0.3)", False, True),
+    (16, 16384, "fhtp.make_bend(17)", False, False),
+    (8, 16384, "fhtp.make_bend(None, 0.3)", True, False),
+    (8, 16385, "fhtp.make_bend(None, 0.3)", True, True),
     (16, 24575, "fhtp.make_bend(None, 0.02)", False, False),
     (16, 24576, "fhtp.make_bend(None, 0.02)", True, True),
-    (32, 32767, "fhtp.make_bend(17)", False, False),
-    (32, 32768, "fhtp.make_bend(17)", False, True),
-    (32, 8191, "fhtp.make_bend(1 << 20)", True, False),
-    (32, 8192, "fhtp.make_bend(1 << 20)", True, True),
+    (32, 40959, "fhtp.make_bend(None, 0.02)", False, False),
+    (32, 40960, "fhtp.make_bend(None, 0.02)", False, True),
+    (32, 16385, "fhtp.make_bend(None, 0.1)", False, True),
+    (32, 24575, "fhtp.make_bend(None, 0.3)", False, False),
+    (32, 24576, "fhtp.make_bend(None, 0.3)", False, True),
+    (32, 49151, "fhtp.make_bend(17)", False, False),
+    (32, 49152, "fhtp.make_bend(17)", False, True),
+    (8, 8191, "fhtp.make_bend(1 << 20)", True, False),
+    (8, 8192, "fhtp.make_bend(1 << 20)", True, True),
+    (32, 8192, "fhtp.make_bend(1 << 20)", True, False),
+    (32, 8193, "fhtp.make_bend(1 << 20)", True, True),
     (64, 60000, "fhtp.make_bend(None, 0.02)", False, False),
     (64, 60000, "fhtp.make_bend(1 << 20)", True, False),
     (256, 4095, "fhtp.make_bend(None, 0.005)", False, False),
