@@ -33,17 +33,17 @@ HBM_PEAK_GBPS = 8000.0
 # otherwise the traffic is unknown and reported as null.
 TRAFFIC = {
     "fht_reg_kernel": {"source": "paper_1912_01884_amd/csrc/fhtp_fht.hip",
-                      "source_sha256": "2f388ffb645cd52891ba82f421392734628ae932985defb45aee7208843c7124",
-                      "fetch_bytes": 46046000, "write_bytes": 137935974},
+                      "source_sha256": "e418c18dd86d555c4aed122dc4e6faabe39f93fbd359dd483b55d15b6356fcb5",
+                      "fetch_bytes": 46048000, "write_bytes": 137929216},
     "dp_pair_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-                     "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
-                     "fetch_bytes": 13993000, "write_bytes": 6653440},
+                     "source_sha256": "59347e5125fd3e758af648f43c3387645e5b48bdeef1af1c5115e3471c535c2c",
+                     "fetch_bytes": 13986000, "write_bytes": 6653440},
     "dp_step_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-                     "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
-                     "fetch_bytes": 8688000, "write_bytes": 6144},
+                     "source_sha256": "59347e5125fd3e758af648f43c3387645e5b48bdeef1af1c5115e3471c535c2c",
+                     "fetch_bytes": 8681000, "write_bytes": 6144},
     "walk": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
-            "source_sha256": "477a594fb01f24b6d2bf0e3b592c1cfec91883ca8704249aaf6c59f2e71a685f",
-            "fetch_bytes": 66340, "write_bytes": 205},
+            "source_sha256": "59347e5125fd3e758af648f43c3387645e5b48bdeef1af1c5115e3471c535c2c",
+            "fetch_bytes": 67570, "write_bytes": 205},
 }
 
 
