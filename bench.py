@@ -33,7 +33,7 @@ HBM_PEAK_GBPS = 8000.0
 # otherwise the traffic is unknown and reported as null.
 TRAFFIC = {
     "fht_reg_kernel": {"source": "paper_1912_01884_amd/csrc/fhtp_fht.hip",
-                      "source_sha256": "e418c18dd86d555c4aed122dc4e6faabe39f93fbd359dd483b55d15b6356fcb5",
+                      "source_sha256": "e1beea3980d52e7f5f6a5887736e075137c6ded74fb613d7d886eb33bac6cca0",
                       "fetch_bytes": 46048000, "write_bytes": 137929216},
     "dp_pair_fixed": {"source": "paper_1912_01884_amd/csrc/fhtp_dp.hip",
                      "source_sha256": "59347e5125fd3e758af648f43c3387645e5b48bdeef1af1c5115e3471c535c2c",

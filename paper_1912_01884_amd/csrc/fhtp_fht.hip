@@ -1108,6 +1108,7 @@ hipError_t launch_reg_any(int p, const RegRun* runs, int count, hipStream_t stre
 
 size_t fht_scratch_bytes(const Geometry& g, int dtype) {
     // (bands of 256 rows no longer use theirs; callers' sizes stay what they were)
+    static_assert(kOnePassMax >= kRegMaxP, "counted wherever two passes use it");
     if (g.p <= kRegMaxP) return 0;
     // [h/128 sub-blocks][2 directions][128 shifts][W]: uint16 for 8-bit pixels
     // (a 128-row line sum is at most 128 * 255), int32 for 16-bit ones
